@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfdtd.so")
-SOURCES = ["fdtd_api.hip", "plain.hip", "systolic.hip", "adjoint.hip", "invariants.hip", "materials.hip",
+SOURCES = ["fdtd_api.hip", "plain.hip", "sweep.hip", "systolic.hip", "adjoint.hip", "invariants.hip", "materials.hip",
            "autotune.hip", "plan.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

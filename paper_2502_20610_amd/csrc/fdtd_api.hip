@@ -487,6 +487,7 @@ int fdtd_destroy(fdtd_ctx* ctx)
     systolic_release(ctx);
     release_material_ids(ctx);
     release_step_graph(ctx);
+    sweep_release(ctx);
     for (int c = 0; c < 6; ++c) {
         if (ctx->field[c]) (void)hipFree(ctx->field[c]);
         if (ctx->field16[c]) (void)hipFree(ctx->field16[c]);
@@ -622,8 +623,7 @@ int fdtd_set_lossy_materials(fdtd_ctx* ctx, const float* eps_x, const float* eps
         (void)hipFree(stage);
     }
     if (e != hipSuccess) return hip_fail(ctx, e, "set_lossy_materials");
-    release_material_ids(ctx);  // the conductive update reads its per-cell arrays
-    return FDTD_OK;
+    return build_material_ids(ctx);
 }
 
 int fdtd_set_fields(fdtd_ctx* ctx, uint32_t comp_mask, const float* const src[6], int where)
@@ -758,7 +758,8 @@ int fdtd_prepare(fdtd_ctx* ctx, int64_t nsteps)
     if (nsteps < 0) return fail(ctx, FDTD_EINVAL, "prepare: nsteps must be >= 0");
     if (nsteps == 0) return FDTD_OK;
     (void)hipSetDevice(ctx->device);
-    if (ctx->scheme == FDTD_SCHEME_PLAIN) return FDTD_OK;
+    if (ctx->scheme == FDTD_SCHEME_PLAIN)
+        return plain_sweeps(ctx, nsteps) && sweep_ready(ctx) ? sweep_prepare(ctx) : FDTD_OK;
     if (ctx->scheme == FDTD_SCHEME_PLAIN_FUSED) return plain_fused_prepare(ctx);
     std::string why;
     if (!systolic_supported(ctx, &why)) return fail(ctx, FDTD_EUNSUPPORTED, "systolic: " + why);

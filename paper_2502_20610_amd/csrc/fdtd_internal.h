@@ -38,6 +38,7 @@ struct PendingTiming {
 
 struct SystolicState;  // defined in systolic.hip
 struct StepGraph;      // defined in plain.hip
+struct SweepState;     // defined in sweep.hip
 
 }  // namespace fdtd
 
@@ -59,7 +60,7 @@ struct fdtd_ctx {
     uint16_t* coef16[3];
     int fexp[6];      // FP16 storage: power-of-two scale exponent per field component
     float* ca[3];     // E decay per step with conductivity; null when lossless
-    float* alt[6];    // second field set of the fused plain step (allocated on first use)
+    float* alt[6];    // second field set of the sweeps (allocated on first use)
     float cH;
 
     std::vector<fdtd::SourceRec> sources;
@@ -93,6 +94,12 @@ struct fdtd_ctx {
     float* mat_tab;   // kMaxMaterials x 3 floats, entry 0 = (+0, +0, +0)
     int nmat;
     bool use_mat;     // FDTD_OPT_MATERIAL_IDS
+    // the same as one byte per cell, and for conductive grids too: the table
+    // then holds (cE, ca), 6 floats an entry; ntab8 = 0 when not available
+    uint8_t* mat_id8;
+    float* mat_tab8;
+    int ntab8;
+    fdtd::SweepState* sweep;
     int tile_wx;      // FDTD_OPT_TILE_X: 0 (the launch's default), 11, 15 or 19
     int auto_wx;      // the default width of the last systolic launch (19 or 15; 0 before)
     bool tune_plain;  // FDTD_OPT_AUTOTUNE_PLAIN
@@ -100,7 +107,7 @@ struct fdtd_ctx {
     // plain schemes: step loops replayed as a HIP graph (FDTD_OPT_GRAPHS)
     bool use_graphs;
     fdtd::StepGraph* graph;
-    long long* d_step;  // the step counter the graph advances (two words)
+    long long* d_step;  // the step counter the graph advances
 
     fdtd::SystolicState* sys;
     int sys_grid;        // persistent workgroups of the last systolic launch
@@ -121,11 +128,24 @@ void timing_end(fdtd_ctx* ctx, PendingTiming* t);
 
 // Plain scheme: advance n steps starting at ctx->step_count (plain.hip).
 int plain_step(fdtd_ctx* ctx, int64_t nsteps);
-// Fused plain scheme: one launch per step into the second field set, whose
-// pointers then trade places with ctx->field (plain.hip).
+// Whether a call of the plain scheme advances the grid by sweeps, given the
+// second field set (plain.hip).
+bool plain_sweeps(const fdtd_ctx* ctx, int64_t nsteps);
+// Fused plain scheme (plain.hip).
 int plain_fused_step(fdtd_ctx* ctx, int64_t nsteps);
-// Allocate the fused step's second field set (plain.hip).
 int plain_fused_prepare(fdtd_ctx* ctx);
+
+// Sweep: several steps per pass into the second field set, whose pointers
+// trade places with ctx->field after every pass (sweep.hip).  FP32 storage.
+bool sweep_supported(const fdtd_ctx* ctx);
+// Whether a scheme that does not need the second field set should sweep: it
+// is there, or fits well (and is then allocated).
+bool sweep_ready(fdtd_ctx* ctx);
+int sweep_prepare(fdtd_ctx* ctx);
+// Advance n steps; timed as `kernel`.  With `even` the state of a call of two
+// steps or more ends in the arrays it started from.
+int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);
+void sweep_release(fdtd_ctx* ctx);
 // Free the captured step graph and its counter (plain.hip).
 void release_step_graph_exec(StepGraph* g);
 void release_step_graph(fdtd_ctx* ctx);

@@ -19,6 +19,8 @@
 // the value that positions outside the grid read.
 #include <string.h>
 
+#include <algorithm>
+
 #include <vector>
 
 #include "fdtd_internal.h"
@@ -31,88 +33,104 @@ constexpr int kSlots = 1024;  // hash slots (at most kMaxMaterials used)
 constexpr int kCand = 64;     // unmatched triples reported per round
 constexpr int kThreads = 256;
 
-__host__ __device__ inline unsigned slot_of(unsigned a, unsigned b, unsigned c)
+// N words of a key: the bits of (cEx, cEy, cEz), with conductivity of
+// (cax, cay, caz) too
+template <int N>
+__host__ __device__ inline unsigned slot_of(const unsigned* k)
 {
-    unsigned h = (a * 0x9E3779B1u) ^ (b * 0x85EBCA77u) ^ (c * 0xC2B2AE3Du);
+    unsigned h = (k[0] * 0x9E3779B1u) ^ (k[1] * 0x85EBCA77u) ^ (k[2] * 0xC2B2AE3Du);
+    if (N == 6) h ^= (k[N - 3] * 0x27D4EB2Fu) ^ (k[N - 2] * 0x165667B1u) ^ (k[N - 1] * 0xD3A2646Du);
     h ^= h >> 15;
     h *= 0x2C1B3C6Du;
     h ^= h >> 13;
     return h & (kSlots - 1);
 }
 
-// keys: kSlots x 3 words (the triple's bits), idx: kSlots entries (-1 empty).
-// Cells that match get their index.  Unmatched triples are reported into a
-// table of kCand slots keyed by a hash of the triple: each wavefront reports
-// up to four distinct triples per launch (one atomic compare-and-swap each,
-// no waiting), so a round finds up to kCand new triples; cand[0] is set when
-// any cell did not match.  cand layout: [0] flag, [1 .. kCand] slot keys,
-// then kCand triples.
-// With H16 the coefficients are binary16 (FP16 storage) and the triple is
+struct Arrays {
+    const void* a[6];  // cE, then ca
+};
+
+// keys: kSlots x N words (an entry's bits), idx: kSlots entries (-1 empty).
+// Cells that match get their index (ids: 4 bytes, may be null; ids8: 1 byte,
+// may be null).  Unmatched entries are reported into a table of kCand slots
+// keyed by a hash of the entry: each wavefront reports up to four distinct
+// ones per launch (one atomic compare-and-swap each, no waiting), so a round
+// finds up to kCand new entries; cand[0] is set when any cell did not match.
+// cand layout: [0] flag, [1 .. kCand] slot keys, then kCand entries.
+// With H16 the coefficients are binary16 (FP16 storage) and the entry is
 // that of their exact FP32 values.
-template <bool H16>
-__global__ __launch_bounds__(kThreads) void classify_kernel(const void* __restrict__ c0v,
-                                                            const void* __restrict__ c1v,
-                                                            const void* __restrict__ c2v, long long n,
+template <bool H16, int N>
+__global__ __launch_bounds__(kThreads) void classify_kernel(Arrays A, long long n,
                                                             const unsigned* __restrict__ keys,
                                                             const int* __restrict__ idx,
                                                             unsigned* __restrict__ ids,
+                                                            uint8_t* __restrict__ ids8,
                                                             unsigned* __restrict__ cand)
 {
-    __shared__ unsigned s_key[kSlots][3];
+    __shared__ unsigned s_key[kSlots][N];
     __shared__ int s_idx[kSlots];
     auto bits = [&](const void* base, long long p) -> unsigned {
         if (H16) return __float_as_uint((float)__builtin_bit_cast(_Float16, ((const uint16_t*)base)[p]));
         return __float_as_uint(((const float*)base)[p]);
     };
     for (int i = threadIdx.x; i < kSlots; i += kThreads) {
-        s_key[i][0] = keys[3 * i];
-        s_key[i][1] = keys[3 * i + 1];
-        s_key[i][2] = keys[3 * i + 2];
+#pragma unroll
+        for (int q = 0; q < N; ++q) s_key[i][q] = keys[N * i + q];
         s_idx[i] = idx[i];
     }
     __syncthreads();
-    int reports = 0;  // wave-uniform: distinct triples this wavefront reported
+    int reports = 0;  // wave-uniform: distinct entries this wavefront reported
     const long long nr = (n + kThreads - 1) / kThreads * kThreads;  // every lane runs every pass
     for (long long p0 = (long long)blockIdx.x * kThreads; p0 < nr; p0 += (long long)gridDim.x * kThreads) {
         const long long p = p0 + threadIdx.x;
         const bool in = p < n;
-        unsigned a = 0, b = 0, c = 0;
+        unsigned k[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) k[q] = 0u;
         int found = -1;
         if (in) {
-            a = bits(c0v, p);
-            b = bits(c1v, p);
-            c = bits(c2v, p);
-            unsigned s = slot_of(a, b, c);
+#pragma unroll
+            for (int q = 0; q < N; ++q) k[q] = bits(A.a[q], p);
+            unsigned s = slot_of<N>(k);
             // the table is at most a quarter full, so an empty slot ends every probe
             for (int probe = 0; probe < kSlots; ++probe) {
                 const int id = s_idx[s];
                 if (id < 0) break;
-                if (s_key[s][0] == a && s_key[s][1] == b && s_key[s][2] == c) {
+                bool same = true;
+#pragma unroll
+                for (int q = 0; q < N; ++q) same = same && s_key[s][q] == k[q];
+                if (same) {
                     found = id;
                     break;
                 }
                 s = (s + 1) & (kSlots - 1);
             }
-            ids[p] = found >= 0 ? (unsigned)found : 0u;
+            if (ids) ids[p] = found >= 0 ? (unsigned)found : 0u;
+            if (ids8) ids8[p] = found >= 0 ? (uint8_t)found : (uint8_t)0;
         }
         unsigned long long miss = __ballot(in && found < 0);
         if (miss && (threadIdx.x & 63) == __ffsll((long long)miss) - 1) cand[0] = 1u;
         while (miss && reports < 4) {
             const int lead = __ffsll((long long)miss) - 1;
-            const unsigned ta = __shfl(a, lead, 64), tb = __shfl(b, lead, 64), tc = __shfl(c, lead, 64);
+            unsigned t[N];
+            bool same = true;
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                t[q] = __shfl(k[q], lead, 64);
+                same = same && k[q] == t[q];
+            }
             if ((int)(threadIdx.x & 63) == lead) {
-                const unsigned h = (slot_of(ta, tb, tc) * 0x9E3779B9u) | 1u;  // never 0 (free)
+                const unsigned h = (slot_of<N>(t) * 0x9E3779B9u) | 1u;  // never 0 (free)
                 const unsigned q = h % (unsigned)kCand;
                 const unsigned prev = atomicCAS(&cand[1 + q], 0u, h);
                 if (prev == 0u) {
-                    unsigned* t = cand + 1 + kCand + 3 * q;
-                    t[0] = ta;
-                    t[1] = tb;
-                    t[2] = tc;
+                    unsigned* d = cand + 1 + kCand + N * q;
+#pragma unroll
+                    for (int c = 0; c < N; ++c) d[c] = t[c];
                 }
             }
-            // lanes holding the same triple are covered by that report
-            miss &= __ballot(!(a == ta && b == tb && c == tc));
+            // lanes holding the same entry are covered by that report
+            miss &= __ballot(!same);
             ++reports;
         }
     }
@@ -128,57 +146,66 @@ int grid_blocks(int64_t n)
 
 void release_material_ids(fdtd_ctx* ctx)
 {
-    if (ctx->mat_id) (void)hipFree(ctx->mat_id);
-    if (ctx->mat_tab) (void)hipFree(ctx->mat_tab);
+    for (void* p : {(void*)ctx->mat_id, (void*)ctx->mat_tab, (void*)ctx->mat_id8, (void*)ctx->mat_tab8})
+        if (p) (void)hipFree(p);
     ctx->mat_id = nullptr;
     ctx->mat_tab = nullptr;
+    ctx->mat_id8 = nullptr;
+    ctx->mat_tab8 = nullptr;
     ctx->nmat = 0;
+    ctx->ntab8 = 0;
 }
 
-int build_material_ids(fdtd_ctx* ctx)
+namespace {
+
+template <typename T>
+bool ensure(T** p, size_t n)
 {
-    ctx->nmat = 0;
-    if (ctx->ca[0]) return FDTD_OK;  // lossless grids only
+    if (*p || hipMalloc(p, n * sizeof(T)) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+
+// Finds the distinct entries of N words and the index of every cell; leaves
+// *count = 0 when there are more than kMaxMaterials.
+template <int N>
+int find_entries(fdtd_ctx* ctx, uint32_t* ids, uint8_t* ids8, std::vector<unsigned>* table, int* count)
+{
+    *count = 0;
     hipError_t e;
-    if (!ctx->mat_id && (e = hipMalloc(&ctx->mat_id, (size_t)ctx->ncell * sizeof(unsigned))) != hipSuccess) {
-        (void)hipGetLastError();
-        ctx->mat_id = nullptr;
-        return FDTD_OK;  // no room: the per-cell arrays serve
-    }
-    if (!ctx->mat_tab && (e = hipMalloc(&ctx->mat_tab, kMaxMaterials * 3 * sizeof(float))) != hipSuccess) {
-        (void)hipGetLastError();
-        ctx->mat_tab = nullptr;
-        return FDTD_OK;
-    }
-    unsigned* d_keys = nullptr;
-    int* d_idx = nullptr;
-    unsigned* d_cand = nullptr;
-    const size_t ncand = 1 + kCand + 3 * kCand;  // flag, slot keys, triples
-    const size_t scratch = kSlots * 3 * sizeof(unsigned) + kSlots * sizeof(int) + ncand * sizeof(unsigned);
+    const size_t ncand = 1 + kCand + N * kCand;  // flag, slot keys, entries
+    const size_t scratch = kSlots * N * sizeof(unsigned) + kSlots * sizeof(int) + ncand * sizeof(unsigned);
     char* d_scratch = nullptr;
     if ((e = hipMalloc(&d_scratch, scratch)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, FDTD_ENOMEM, "material table: scratch allocation failed");
     }
-    d_keys = (unsigned*)d_scratch;
-    d_idx = (int*)(d_keys + kSlots * 3);
-    d_cand = (unsigned*)(d_idx + kSlots);
-
-    std::vector<unsigned> tab(3, 0u);  // entry 0: (+0, +0, +0)
-    std::vector<unsigned> keys(kSlots * 3), cand(ncand);
+    unsigned* d_keys = (unsigned*)d_scratch;
+    int* d_idx = (int*)(d_keys + kSlots * N);
+    unsigned* d_cand = (unsigned*)(d_idx + kSlots);
+    const bool h16 = ctx->storage == FDTD_FP16_STORAGE;
+    Arrays A{};
+    for (int q = 0; q < 3; ++q) {
+        A.a[q] = h16 ? (const void*)ctx->coef16[q] : (const void*)ctx->coef[q];
+        A.a[3 + q] = ctx->ca[q];
+    }
+    std::vector<unsigned>& tab = *table;
+    tab.assign(N, 0u);  // entry 0: all +0
+    std::vector<unsigned> keys(kSlots * N), cand(ncand);
     const std::vector<unsigned> cand0(ncand, 0u);
     std::vector<int> idx(kSlots);
     bool ok = false;
     e = hipSuccess;
     for (int round = 0; round <= kMaxMaterials && e == hipSuccess; ++round) {
-        const int nm = (int)tab.size() / 3;
+        const int nm = (int)tab.size() / N;
         std::fill(idx.begin(), idx.end(), -1);
         std::fill(keys.begin(), keys.end(), 0u);
         for (int m = 0; m < nm; ++m) {
-            unsigned s = slot_of(tab[3 * m], tab[3 * m + 1], tab[3 * m + 2]);
+            unsigned s = slot_of<N>(&tab[N * m]);
             while (idx[s] >= 0) s = (s + 1) & (kSlots - 1);
             idx[s] = m;
-            for (int q = 0; q < 3; ++q) keys[3 * s + q] = tab[3 * m + q];
+            for (int q = 0; q < N; ++q) keys[N * s + q] = tab[N * m + q];
         }
         if ((e = hipMemcpyAsync(d_keys, keys.data(), keys.size() * sizeof(unsigned), hipMemcpyHostToDevice,
                                 ctx->stream)) != hipSuccess ||
@@ -187,12 +214,9 @@ int build_material_ids(fdtd_ctx* ctx)
             (e = hipMemcpyAsync(d_cand, cand0.data(), ncand * sizeof(unsigned), hipMemcpyHostToDevice,
                                 ctx->stream)) != hipSuccess)
             break;
-        const bool h16 = ctx->storage == FDTD_FP16_STORAGE;
-        const void* cs[3];
-        for (int q = 0; q < 3; ++q) cs[q] = h16 ? (const void*)ctx->coef16[q] : (const void*)ctx->coef[q];
-        hipLaunchKernelGGL(h16 ? classify_kernel<true> : classify_kernel<false>, dim3(grid_blocks(ctx->ncell)),
-                           dim3(kThreads), 0, ctx->stream, cs[0], cs[1], cs[2], (long long)ctx->ncell, d_keys,
-                           d_idx, ctx->mat_id, d_cand);
+        const auto kern = N == 6 ? classify_kernel<false, N> : h16 ? classify_kernel<true, N> : classify_kernel<false, N>;
+        hipLaunchKernelGGL(kern, dim3(grid_blocks(ctx->ncell)), dim3(kThreads), 0, ctx->stream, A,
+                           (long long)ctx->ncell, d_keys, d_idx, ids, ids8, d_cand);
         if ((e = hipGetLastError()) != hipSuccess) break;
         if ((e = hipMemcpyAsync(cand.data(), d_cand, cand.size() * sizeof(unsigned), hipMemcpyDeviceToHost,
                                 ctx->stream)) != hipSuccess ||
@@ -202,28 +226,57 @@ int build_material_ids(fdtd_ctx* ctx)
             ok = true;
             break;
         }
-        for (int i = 0; i < kCand && (int)tab.size() / 3 <= kMaxMaterials; ++i) {
+        for (int i = 0; i < kCand && (int)tab.size() / N <= kMaxMaterials; ++i) {
             if (cand[1 + i] == 0) continue;  // slot not claimed
-            const unsigned* t = &cand[1 + kCand + 3 * i];
+            const unsigned* t = &cand[1 + kCand + N * i];
             bool have = false;
-            for (size_t m = 0; m < tab.size() / 3 && !have; ++m)
-                have = tab[3 * m] == t[0] && tab[3 * m + 1] == t[1] && tab[3 * m + 2] == t[2];
-            if (!have) tab.insert(tab.end(), t, t + 3);
+            for (size_t m = 0; m < tab.size() / N && !have; ++m) have = std::equal(t, t + N, &tab[N * m]);
+            if (!have) tab.insert(tab.end(), t, t + N);
         }
-        if ((int)tab.size() / 3 > kMaxMaterials) break;  // too many: the per-cell arrays serve
-    }
-    if (ok && e == hipSuccess) {
-        std::vector<unsigned> full(kMaxMaterials * 3, 0u);
-        std::copy(tab.begin(), tab.end(), full.begin());
-        e = hipMemcpyAsync(ctx->mat_tab, full.data(), full.size() * sizeof(unsigned), hipMemcpyHostToDevice,
-                           ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e == hipSuccess) ctx->nmat = (int)tab.size() / 3;
+        if ((int)tab.size() / N > kMaxMaterials) break;  // too many: the per-cell arrays serve
     }
     (void)hipFree(d_scratch);
     if (e != hipSuccess) return hip_fail(ctx, e, "material table");
-    // too many materials: the per-cell arrays serve, the index array goes
-    if (ctx->nmat == 0) release_material_ids(ctx);
+    if (ok) *count = (int)tab.size() / N;
+    return FDTD_OK;
+}
+
+}  // namespace
+
+int build_material_ids(fdtd_ctx* ctx)
+{
+    ctx->nmat = 0;
+    ctx->ntab8 = 0;
+    const bool lossy = ctx->ca[0] != nullptr;
+    const size_t nc = (size_t)ctx->ncell;
+    const int N = lossy ? 6 : 3;
+    if (lossy) release_material_ids(ctx);  // the systolic scheme streams a conductive grid's arrays
+    if (!lossy && (!ensure(&ctx->mat_id, nc) || !ensure(&ctx->mat_tab, (size_t)kMaxMaterials * 3)))
+        return FDTD_OK;  // no room: the per-cell arrays serve
+    // (a change between lossless and conductive goes through release_material_ids)
+    const bool bytes = ctx->storage == FDTD_FP32 && ensure(&ctx->mat_id8, nc) &&
+                       ensure(&ctx->mat_tab8, (size_t)kMaxMaterials * 6);
+    if (lossy && !bytes) return FDTD_OK;
+    std::vector<unsigned> tab;
+    int count = 0;
+    int rc = lossy ? find_entries<6>(ctx, nullptr, ctx->mat_id8, &tab, &count)
+                   : find_entries<3>(ctx, ctx->mat_id, bytes ? ctx->mat_id8 : nullptr, &tab, &count);
+    if (rc) return rc;
+    if (count > 0) {
+        tab.resize((size_t)kMaxMaterials * N, 0u);
+        hipError_t e = hipSuccess;
+        if (!lossy)
+            e = hipMemcpyAsync(ctx->mat_tab, tab.data(), tab.size() * sizeof(unsigned), hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess && bytes)
+            e = hipMemcpyAsync(ctx->mat_tab8, tab.data(), tab.size() * sizeof(unsigned), hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess) return hip_fail(ctx, e, "material table");
+        ctx->nmat = lossy ? 0 : count;
+        ctx->ntab8 = bytes ? count : 0;
+    } else {
+        // too many materials: the per-cell arrays serve, the indices go
+        release_material_ids(ctx);
+    }
     return FDTD_OK;
 }
 

@@ -1,0 +1,85 @@
+"""Sweeps (several steps per pass over the grid) against the FP32 oracle, bit
+for bit: grids at the edges of the 64-lane, 16- and 32-row tiles and smaller
+than one, every length of pass and their mixtures, coefficients as arrays and
+as table indices, lossless and conductive, and blocks that meet more sources
+than they keep at hand."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_20610_amd import fdtd
+from paper_2502_20610_amd import workloads as wl
+from tests.test_gpu_parity import assert_bitwise
+
+pytestmark = pytest.mark.gpu
+PEC, PER = 0, 1
+
+SHAPES = [((1, 1, 1), (PER, PER, PER)), ((3, 2, 70), (PEC, PER, PEC)), ((9, 22, 54), (PEC, PEC, PEC)),
+          ((12, 23, 55), (PER, PEC, PER)), ((31, 6, 56), (PEC, PER, PEC)), ((7, 33, 113), (PER, PER, PEC)),
+          ((40, 65, 20), (PEC, PEC, PER))]
+
+
+def _materials(kind, shape, rng):
+    """(eps, sigma or None): `table` few distinct cells, `arrays` all distinct."""
+    cells = shape[0] * shape[1] * shape[2]
+    few = rng.integers(0, 5, shape)
+    if "arrays" in kind:
+        eps = (1.0 + np.arange(cells, dtype=np.float32).reshape(shape) / np.float32(64)).astype(np.float32)
+    else:
+        eps = np.float32([1.0, 2.08, 3.5, 7.0, 12.25])[few]
+    sigma = None
+    if "lossy" in kind:
+        sigma = np.float32([0.0, 0.01, 0.1, 0.3, 0.4])[few[::-1]]
+    return np.ascontiguousarray(eps), None if sigma is None else np.ascontiguousarray(sigma)
+
+
+@pytest.mark.parametrize("kind", ["table", "arrays", "lossy table", "lossy arrays"])
+@pytest.mark.parametrize("shape,bc", SHAPES)
+def test_sweep_bitwise(shape, bc, kind):
+    rng = np.random.default_rng(sum(shape) + len(kind))
+    eps, sigma = _materials(kind, shape, rng)
+    fields = wl.zero_pec([rng.uniform(-1, 1, shape).astype(np.float32) for _ in range(6)], bc)
+    wave = rng.uniform(-1, 1, 40).astype(np.float32)
+    # interior, last and first cells (off the walls); two on one cell, one that starts late
+    cells = [tuple(n // 2 for n in shape), tuple(n - 1 for n in shape), tuple(n // 2 for n in shape)]
+    sources = [wl.dipole(c % 3, *p, wave[c:], first_step=5 * (c == 1)) for c, p in enumerate(cells)
+               if all(bc[a] == PER or p[a] > 0 for a in range(3))]
+    for scheme in ("plain", "plain_fused"):
+        sim = fdtd.Simulation(shape, 0.5, 1.0, bc, scheme=scheme)
+        try:
+            sim.set_materials(eps, sigma=sigma)
+            sim.set_fields(fields)
+            for s in sources:
+                sim.add_source(s["comp"], s["i"], s["j"], s["k"], s["waveform"], s["first_step"])
+            done = 0
+            for n in (2, 1, 3, 5, 4, 11):
+                sim.step(n)
+                done += n
+            got = sim.read_fields()
+        finally:
+            sim.close()
+        ref = oracle.run(fields, [eps] * 3, bc, 0.5, 1.0, done, sources=sources, dtype=np.float32,
+                         sigma=None if sigma is None else [sigma] * 3)
+        assert_bitwise(got, ref, "%s %s %s %s" % (scheme, shape, bc, kind))
+
+
+def test_sweep_many_sources():
+    """70 and 200 sources in one tile, some sharing a cell and a component."""
+    shape, bc = (12, 20, 30), (PEC, PER, PEC)
+    rng = np.random.default_rng(3)
+    eps = np.full(shape, 2.08, np.float32)
+    zero = [np.zeros(shape, np.float32) for _ in range(6)]
+    for count in (70, 200):
+        sources = [wl.dipole(2, *(int(rng.integers(1, min(n, 6))) for n in shape),
+                             rng.uniform(-1, 1, 12).astype(np.float32)) for _ in range(count)]
+        sim = fdtd.Simulation(shape, 0.5, 1.0, bc, scheme="plain_fused")
+        try:
+            sim.set_materials(eps)
+            for s in sources:
+                sim.add_source(s["comp"], s["i"], s["j"], s["k"], s["waveform"])
+            sim.step(13)
+            got = sim.read_fields()
+        finally:
+            sim.close()
+        ref = oracle.run(zero, [eps] * 3, bc, 0.5, 1.0, 13, sources=sources, dtype=np.float32)
+        assert_bitwise(got, ref, "%d sources" % count)
