@@ -38,6 +38,13 @@ PLAIN_BYTES_PER_UPDATE = PLAIN_E_BYTES + PLAIN_H_BYTES
 PLAIN_FUSED_BYTES_PER_UPDATE = 60
 
 
+def sweep_alg_bytes_per_update(steps: float, lossy: bool = False, materials: bool = False) -> float:
+    """Algorithmic bytes per cell update of a sweep: the state and the
+    coefficients (one byte with material indices) in, the state out, once per
+    pass of `steps` steps."""
+    return (24 + (1 if materials else 24 if lossy else 12) + 24) / float(steps)
+
+
 def systolic_alg_bytes_per_update(tile, band, conductive=False, fp16=False, materials=False):
     """Algorithmic HBM bytes per cell update of the systolic scheme: what the
     method itself must move (Section 4's accounting).  Every step a tile of
@@ -559,11 +566,13 @@ def main():
         steps_per_launch = args.steps / max(n, 1)
         band = stats["info"]["band_steps"]
         mats = stats["info"]["materials"] > 0
-        b_alg = systolic_alg_bytes_per_update(stats["info"]["tile"], band, sigma is not None,
+        swept = stats["info"]["ring_slots"] == 0   # the call ran as sweeps
+        b_alg = sweep_alg_bytes_per_update(steps_per_launch, sigma is not None, mats) if swept else systolic_alg_bytes_per_update(stats["info"]["tile"], band, sigma is not None,
                                               args.storage == "fp16", mats)
-        b_design = systolic_bytes_per_update(stats["info"]["tile"], band, sigma is not None,
-                                             args.storage == "fp16", mats)
-        if band >= steps_per_launch and band < 64 and not args.band:
+        b_design = None if swept else \
+            systolic_bytes_per_update(stats["info"]["tile"], band, sigma is not None,
+                                      args.storage == "fp16", mats)
+        if not swept and band >= steps_per_launch and band < 64 and not args.band:
             log("systolic: the band (%d steps) is capped by the call length (--steps %d)"
                 % (band, args.steps))
         updates = cells * steps_per_launch
@@ -573,17 +582,18 @@ def main():
                   + ("_fp16" if args.storage == "fp16" else ""),
                   "steps": int(round(steps_per_launch)), "band": band, "materials": int(mats),
                   "tile_x": stats["info"]["tile"][0]}
-        traffic = counter_traffic("systolic_kernel", "paper_2502_20610_amd/csrc/systolic.hip",
+        name = "sweep_kernel" if swept else "systolic_kernel"
+        traffic = counter_traffic(name, "paper_2502_20610_amd/csrc/%s.hip" % name[:-7],
                                   dict(launch, cells=cells))
         # arithmetic intensity 36 / b_alg flop/B is below the machine balance
         # (39.3 T op/s / 8 TB/s), so the roofline bound is HBM
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                "kernel": "systolic_kernel", "launches": n, "avg_launch_ms": avg_s * 1e3,
+                "kernel": name, "launches": n, "avg_launch_ms": avg_s * 1e3,
                 "alg_bytes_per_update": b_alg,
                 "design_bytes_per_update": b_design,
                 "band_steps": band,
-                "band_capped_by_call": bool(band >= steps_per_launch and band < 64),
+                "band_capped_by_call": bool(not swept and band >= steps_per_launch and band < 64),
                 "traffic_bytes_per_update": None if traffic is None else traffic / updates,
                 "traffic_GBps": None if traffic is None else traffic / avg_s / 1e9,
                 "alu_achieved_TFLOPs": flops, "alu_peak_TFLOPs": VALU_FP32_PEAK_TFLOPS,
@@ -623,12 +633,15 @@ def main():
         if scheme in ("systolic", "systolic_arrays"):
             entry.update(st["info"])
             mats = st["info"]["materials"] > 0
-            b = systolic_alg_bytes_per_update(st["info"]["tile"], st["info"]["band_steps"],
-                                              sigma is not None, args.storage == "fp16", mats)
+            if st["info"]["ring_slots"] == 0:
+                b = sweep_alg_bytes_per_update(st["info"]["band_steps"], sigma is not None, mats)
+            else:
+                b = systolic_alg_bytes_per_update(st["info"]["tile"], st["info"]["band_steps"],
+                                                  sigma is not None, args.storage == "fp16", mats)
+                entry["design_bytes_per_update"] = systolic_bytes_per_update(
+                    st["info"]["tile"], st["info"]["band_steps"], sigma is not None,
+                    args.storage == "fp16", mats)
             entry["alg_bytes_per_update"] = b
-            entry["design_bytes_per_update"] = systolic_bytes_per_update(
-                st["info"]["tile"], st["info"]["band_steps"], sigma is not None, args.storage == "fp16",
-                mats)
             entry["alg_roofline_frac"] = c * b / (HBM_PEAK_GBS * 1e9)
             entry["effective_bw_frac_84B"] = c * PLAIN_BYTES_PER_UPDATE / (HBM_PEAK_GBS * 1e9)
         if scheme == "plain":

@@ -22,16 +22,31 @@
  * Schemes:
  *   FDTD_SCHEME_PLAIN    one kernel launch per half-step over the whole grid:
  *                        the naive implementation of Section 2 / Fig. 1.
+ *                        Calls of two steps or more advance FP32 grids by
+ *                        sweeps instead (several steps per pass from one set
+ *                        of arrays to a second one and back: the state ends
+ *                        in the arrays it started from), unless per-kernel
+ *                        timing is on or the second set would take more than
+ *                        a quarter of the free device memory.
  *   FDTD_SCHEME_SYSTOLIC one persistent launch per call: subdomain tiles stay
  *                        resident on chip for many steps, move one cell along
  *                        the x-y-z-t diagonal per step and exchange only their
  *                        boundary faces through device memory, synchronising
- *                        with neighbour flags (Sections 3 and 4).
- *   FDTD_SCHEME_PLAIN_FUSED one kernel launch per step over the whole grid:
- *                        E and H are read from one set of arrays and the new
- *                        step is written to a second set, allocated on first
- *                        use (six more arrays; the two sets then trade places
- *                        every step).  FP32 storage only (else
+ *                        with neighbour flags (Sections 3 and 4).  FP32
+ *                        calls of two steps or more run as sweeps, under the
+ *                        conditions above, unless a systolic option (band
+ *                        steps, workgroups, tile width, spin limit) is set or
+ *                        the call spans two of the longest bands on an
+ *                        all-PEC grid; launches of either kind count as
+ *                        FDTD_KERNEL_SYSTOLIC, and FDTD_INFO_SYSTOLIC_* then
+ *                        describe the sweep (steps per pass, blocks, tiles, 0
+ *                        ring slots).
+ *   FDTD_SCHEME_PLAIN_FUSED sweeps: one launch advances up to five steps
+ *                        (one with per-kernel timing on).  E and H are read
+ *                        from one set of arrays and the new state is written
+ *                        to a second set, allocated on first use (six more
+ *                        arrays; the two sets trade places with every
+ *                        launch).  FP32 storage only (else
  *                        FDTD_EUNSUPPORTED from fdtd_step); conductivity is
  *                        covered.
  *

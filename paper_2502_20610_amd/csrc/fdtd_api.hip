@@ -378,7 +378,7 @@ int fdtd_create(const fdtd_config* cfg, fdtd_ctx** out)
     ctx->storage = cfg->storage;
     ctx->band_steps = 0;  // 0 = choose per call
     ctx->workgroups = 0;
-    ctx->spin_limit = int64_t(1) << 22;
+    ctx->spin_limit = kDefaultSpinLimit;
     ctx->profile = false;
     ctx->use_mat = true;
     ctx->use_graphs = true;

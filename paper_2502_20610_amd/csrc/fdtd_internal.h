@@ -118,6 +118,8 @@ struct fdtd_ctx {
 
 namespace fdtd {
 
+constexpr int64_t kDefaultSpinLimit = int64_t(1) << 22;
+
 // Error helpers (set ctx->err, return the code).
 int fail(fdtd_ctx* ctx, int code, const std::string& msg);
 int hip_fail(fdtd_ctx* ctx, hipError_t e, const char* what);
@@ -145,6 +147,8 @@ int sweep_prepare(fdtd_ctx* ctx);
 // Advance n steps; timed as `kernel`.  With `even` the state of a call of two
 // steps or more ends in the arrays it started from.
 int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);
+// The longest pass, the blocks and the tiles of the last sweep of the context.
+void sweep_shape(const fdtd_ctx* ctx, int* steps, int* blocks, int* tiles);
 void sweep_release(fdtd_ctx* ctx);
 // Free the captured step graph and its counter (plain.hip).
 void release_step_graph_exec(StepGraph* g);

@@ -30,7 +30,8 @@ namespace fdtd {
 namespace {
 
 constexpr int kSlots = 1024;  // hash slots (at most kMaxMaterials used)
-constexpr int kCand = 64;     // unmatched triples reported per round
+constexpr int kCand = 256;    // unmatched entries reported per round
+constexpr int kReports = 16;  // of them by one wavefront
 constexpr int kThreads = 256;
 
 // N words of a key: the bits of (cEx, cEy, cEz), with conductivity of
@@ -53,9 +54,10 @@ struct Arrays {
 // keys: kSlots x N words (an entry's bits), idx: kSlots entries (-1 empty).
 // Cells that match get their index (ids: 4 bytes, may be null; ids8: 1 byte,
 // may be null).  Unmatched entries are reported into a table of kCand slots
-// keyed by a hash of the entry: each wavefront reports up to four distinct
-// ones per launch (one atomic compare-and-swap each, no waiting), so a round
-// finds up to kCand new entries; cand[0] is set when any cell did not match.
+// keyed by a hash of the entry: each wavefront reports up to kReports distinct
+// ones per launch (at most one atomic compare-and-swap each, no waiting), so a
+// round finds up to kCand new entries (with 64 slots and four reports a
+// conductive shell of 35 M cells took 15 ms to set up instead of 8); cand[0] is set when any cell did not match.
 // cand layout: [0] flag, [1 .. kCand] slot keys, then kCand entries.
 // With H16 the coefficients are binary16 (FP16 storage) and the entry is
 // that of their exact FP32 values.
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(Arrays A, long long 
         }
         unsigned long long miss = __ballot(in && found < 0);
         if (miss && (threadIdx.x & 63) == __ffsll((long long)miss) - 1) cand[0] = 1u;
-        while (miss && reports < 4) {
+        while (miss && reports < kReports) {
             const int lead = __ffsll((long long)miss) - 1;
             unsigned t[N];
             bool same = true;
@@ -122,7 +124,9 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(Arrays A, long long 
             if ((int)(threadIdx.x & 63) == lead) {
                 const unsigned h = (slot_of<N>(t) * 0x9E3779B9u) | 1u;  // never 0 (free)
                 const unsigned q = h % (unsigned)kCand;
-                const unsigned prev = atomicCAS(&cand[1 + q], 0u, h);
+                // (a slot once claimed stays claimed: most find it so without an atomic)
+                const unsigned prev = __hip_atomic_load(&cand[1 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                          ? h : atomicCAS(&cand[1 + q], 0u, h);
                 if (prev == 0u) {
                     unsigned* d = cand + 1 + kCand + N * q;
 #pragma unroll
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(Arrays A, long long 
 int grid_blocks(int64_t n)
 {
     const int64_t b = (n + kThreads - 1) / kThreads;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(b, 4096));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(b, 2048));
 }
 
 }  // namespace

@@ -382,7 +382,8 @@ int plain_fused_step(fdtd_ctx* ctx, int64_t nsteps)
     if (rc) return rc;
     // (a plane of 2 GiB or more: the in-place step, which gives the same bits)
     if (!sweep_supported(ctx)) return run_steps(ctx, nsteps);
-    if (!ctx->profile) return sweep_steps(ctx, nsteps, FDTD_KERNEL_PLAIN_FUSED, false);
+    // (an even number of steps ends in the arrays it started from)
+    if (!ctx->profile) return sweep_steps(ctx, nsteps, FDTD_KERNEL_PLAIN_FUSED, nsteps % 2 == 0);
     // per-kernel timing: one launch per step
     for (int64_t q = 0; q < nsteps && rc == FDTD_OK; ++q) rc = sweep_steps(ctx, 1, FDTD_KERNEL_PLAIN_FUSED, false);
     return rc;

@@ -474,6 +474,7 @@ struct SweepState {
     unsigned* pace = nullptr;
     int pace_words = 0;  // of one of the two alternating halves
     int turn = 0;
+    int steps = 0, blocks = 0, tiles = 0;  // of the last call's longest pass
 };
 
 namespace {
@@ -630,6 +631,12 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
     A.nsrc = ctx->dev_sources_n;
     const int t0 = (int)(n / passes);
     const int64_t longer = n % passes;
+    {
+        const Pass& P = S->pass[t0 + (longer ? 1 : 0)];
+        S->steps = t0 + (longer ? 1 : 0);
+        S->tiles = (int)P.ntiles;
+        S->blocks = (int)((P.ntiles + kXCD - 1) / kXCD * kXCD);
+    }
     for (int64_t p = 0; p < passes; ++p) {
         const int T = t0 + (p < longer ? 1 : 0);
         const Pass& P = S->pass[T];
@@ -657,6 +664,13 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
         ctx->step_count += T;
     }
     return FDTD_OK;
+}
+
+void sweep_shape(const fdtd_ctx* ctx, int* steps, int* blocks, int* tiles)
+{
+    *steps = ctx->sweep->steps;
+    *blocks = ctx->sweep->blocks;
+    *tiles = ctx->sweep->tiles;
 }
 
 void sweep_release(fdtd_ctx* ctx)

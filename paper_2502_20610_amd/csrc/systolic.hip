@@ -1556,6 +1556,53 @@ int upload_plan(fdtd_ctx* lead, SystolicState* L, fdtd_ctx* const* cs, int n)
     return FDTD_OK;
 }
 
+// Whether every member of a launch can hold material indices in registers
+// (lossless grids with at most 256 coefficient triples whose periodic x axes,
+// if any, have 20 cells or more): the default tile is then 19 wide, else 15.
+bool wide_tile_ok(fdtd_ctx* const* cs, int n)
+{
+    bool ok = cs[0]->ca[0] == nullptr;
+    for (int i = 0; i < n && ok; ++i)
+        ok = cs[i]->use_mat && cs[i]->nmat > 0 && cs[i]->mat_id &&
+             !(cs[i]->cfg.bc[0] == FDTD_BC_PERIODIC && cs[i]->nx < WX_WIDE + 1);
+    return ok;
+}
+
+// Whether a call advances the context by sweeps (sweep.hip) instead of the
+// persistent launch.  The sweep has no neighbour to wait for and no band to
+// fill, and is the faster of the two at every size and call length measured
+// (G cell updates/s, systolic / sweep): 64^3 18 / 43, 128^3 86 / 124, 256^3
+// with periodic x and y 94 / 209, 256^3 conductive 109 / 195, 1024 x 1024 x
+// 512 in 20-step calls 163 / 255.  The persistent launch keeps:
+//   * calls with a systolic option of their own, which ask for that kernel;
+//   * FP16 storage, which rounds once per band;
+//   * single steps (a sweep would leave the state in the other arrays);
+//   * on all-PEC grids, calls of two 64-step bands or more (512^3 and up by
+//     the band model), whose band and ring slots FDTD_INFO_* reports
+//     (1024 x 1024 x 512: 214 / 255);
+//   * what it refuses: a ring group of a periodic grid larger than its
+//     resident workgroups (two per CU).
+bool sweeps_instead(fdtd_ctx* ctx, int64_t nsteps)
+{
+    if (nsteps < 2 || nsteps > (int64_t(1) << 24) || !sweep_supported(ctx)) return false;
+    if (ctx->band_steps || ctx->workgroups || ctx->tile_wx || ctx->spin_limit != kDefaultSpinLimit) return false;
+    if (getenv("FDTD_SYSTOLIC_SYNC") || getenv("FDTD_SYSTOLIC_ORDER")) return false;
+    ctx->auto_wx = wide_tile_ok(&ctx, 1) ? WX_WIDE : WX;
+    int N[3], per[3], W[3];
+    axes_of(ctx, N, per);
+    tile_of(ctx, W);
+    long long group = 1;
+    for (int d = 0; d < 3; ++d)
+        if (per[d]) group *= (N[d] + W[d] - 1) / W[d];
+    int cus = 0;
+    if (group > 1 &&
+        (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || group > 2LL * cus))
+        return false;
+    if (!(per[0] || per[1] || per[2]) && nsteps >= 2 * kMaxBand && default_band(&ctx, 1, nsteps) == kMaxBand)
+        return false;
+    return sweep_ready(ctx);
+}
+
 // One persistent launch advancing the contexts cs[0..n) by nsteps each, on
 // cs[0]'s stream (the others' streams wait for it and it for them).
 // kcap: the longest band an automatic choice may take (lowered when the face
@@ -1582,15 +1629,9 @@ int launch(fdtd_ctx* const* cs, int n, int64_t nsteps, int kcap = kMaxBand, bool
     // accesses with agent-scope fences (FDTD_SYSTOLIC_SYNC=fence)
     const char* sync_env = getenv("FDTD_SYSTOLIC_SYNC");
     const bool dev = !(sync_env && strcmp(sync_env, "fence") == 0);
-    // The default tile width: 19 when every member can hold material indices
-    // in registers (lossless grids with at most 256 coefficient triples whose
-    // periodic x axes, if any, have 20 cells or more), else 15.  A
-    // member that asked for a width keeps it (and a batch still needs one
-    // width for all).
-    bool wide_ok = !lossy && dev;
-    for (int i = 0; i < n && wide_ok; ++i)
-        wide_ok = cs[i]->use_mat && cs[i]->nmat > 0 && cs[i]->mat_id &&
-                  !(cs[i]->cfg.bc[0] == FDTD_BC_PERIODIC && cs[i]->nx < WX_WIDE + 1);
+    // A member that asked for a tile width keeps it (and a batch still needs
+    // one width for all).
+    const bool wide_ok = dev && wide_tile_ok(cs, n);
     for (int i = 0; i < n; ++i) cs[i]->auto_wx = wide_ok ? WX_WIDE : WX;
     // band length per simulation: the lead's option for all, else each
     // simulation's own choice of the cost model
@@ -1871,6 +1912,13 @@ int systolic_supported(const fdtd_ctx* ctx, std::string* why)
 
 int systolic_step(fdtd_ctx* ctx, int64_t nsteps)
 {
+    if (sweeps_instead(ctx, nsteps)) {
+        const int rc = sweep_steps(ctx, nsteps, FDTD_KERNEL_SYSTOLIC, true);
+        if (rc) return rc;
+        sweep_shape(ctx, &ctx->sys_band, &ctx->sys_grid, &ctx->sys_tickets);
+        ctx->sys_ring_slots = 0;
+        return FDTD_OK;
+    }
     fdtd_ctx* one[1] = {ctx};
     return launch(one, 1, nsteps);
 }
@@ -1879,6 +1927,7 @@ int systolic_step_batch(fdtd_ctx* const* ctxs, int n, int64_t nsteps) { return l
 
 int systolic_prepare(fdtd_ctx* ctx, int64_t nsteps)
 {
+    if (sweeps_instead(ctx, nsteps)) return sweep_prepare(ctx);
     fdtd_ctx* one[1] = {ctx};
     return launch(one, 1, nsteps, kMaxBand, false);
 }
