@@ -12,12 +12,13 @@ Denormals stay IEEE (no -ffast-math, no flush-to-zero).
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfdtd.so")
-SOURCES = ["fdtd_api.hip", "plain.hip", "sweep.hip", "systolic.hip", "adjoint.hip", "invariants.hip", "materials.hip",
+SOURCES = ["sweep.hip", "systolic.hip", "fdtd_api.hip", "plain.hip", "adjoint.hip", "invariants.hip", "materials.hip",
            "autotune.hip", "plan.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -29,9 +30,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 def build(verbose: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
-    for src in SOURCES:
-        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
+    objs = [os.path.join(objdir, os.path.splitext(src)[0] + ".o") for src in SOURCES]
+
+    def compile_one(src, obj):
         cmd = [HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
@@ -42,7 +43,9 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed on %s" % src)
         if verbose and err.strip():
             sys.stderr.write(err + "\n")
-        objs.append(obj)
+
+    with ThreadPoolExecutor(4) as pool:
+        list(pool.map(compile_one, SOURCES, objs))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp]
     subprocess.run(cmd, check=True, capture_output=not verbose)

@@ -140,6 +140,25 @@ __global__ void adj_grad_kernel(const float* __restrict__ lEx, const float* __re
     }
 }
 
+// The same for `steps` reverse steps at once: lE of the l-th of them is record
+// l of `back` (3 x design cells), its history record ch - l * (3 or 6) cells.
+// One read of each and one of g for the whole run of steps, the terms in the
+// order of the steps.
+template <bool LOSSY>
+__global__ void adj_grad_run_kernel(const float* __restrict__ back, const float* __restrict__ ch, long long nb,
+                                    int steps, double* __restrict__ g)
+{
+    constexpr int NR = LOSSY ? 6 : 3;
+    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < NR * nb;
+         q += (long long)gridDim.x * blockDim.x) {
+        const long long e = q < 3 * nb ? q : q - 3 * nb;
+        double s = g[q];
+#pragma unroll 8
+        for (int l = 0; l < steps; ++l) s += (double)back[l * 3 * nb + e] * (double)ch[q - l * NR * nb];
+        g[q] = s;
+    }
+}
+
 // dJ/deps_c = -g_c cE_c^2 dx / dt over the design box (0 where cE is pinned);
 // with conductivity (ca non-null, cE then being B)
 // dJ/deps_c = (dx / dt) B ((1 - A) gA_c - B gB_c).  With iso the three
@@ -273,14 +292,15 @@ void column_grid(const fdtd_ctx* ctx, dim3* grid, int* xchunk)
 // Device buffers of one adjoint call, freed on every exit path.
 struct Work {
     float* ckpt = nullptr;   // checkpoints of segments 0..nseg-2, then the final state
-    float* lam = nullptr;    // 6 adjoint fields
+    float* lam = nullptr;    // 6 adjoint fields (12 with sweeps)
     double* F = nullptr;     // monitor transform, re/im
     float* hist = nullptr;   // S x (3 or 6) x design cells: CH(H^{n-1/2}) (and E^{n-1})
     double* g = nullptr;     // (3 or 6) x design cells: dJ/dcE (and dJ/dA)
     float* out = nullptr;    // 3 x design cells (host destination only)
+    float* back = nullptr;   // sweeps: adjoint E over the design box, one record per step of a run
     ~Work()
     {
-        for (void* p : {(void*)ckpt, (void*)lam, (void*)F, (void*)hist, (void*)g, (void*)out})
+        for (void* p : {(void*)ckpt, (void*)lam, (void*)F, (void*)hist, (void*)g, (void*)out, (void*)back})
             if (p) (void)hipFree(p);
     }
 };
@@ -363,6 +383,39 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
         }
         return hipSuccess;
     };
+    // Sweeps where the grid and the memory allow them (a second set of fields
+    // and of adjoint fields); the one-step kernels otherwise, and for a single
+    // step.  Same operations on every cell: the results are the same.
+    bool swept = N > 1 && sweep_hooked_ready(ctx);
+    // reverse steps between two additions to the gradient: records of 64 MB at most
+    const int64_t run = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(N, 64), (int64_t)(64e6 / (12.0 * (double)ndes))));
+    if (swept) {
+        float* twice = nullptr;
+        if (hipMalloc(&twice, 12 * nc * sizeof(float)) == hipSuccess &&
+            hipMalloc(&w.back, (size_t)run * 3 * (size_t)ndes * sizeof(float)) == hipSuccess) {
+            (void)hipFree(w.lam);
+            w.lam = twice;
+        } else {
+            (void)hipGetLastError();
+            if (twice) (void)hipFree(twice);
+            swept = false;
+        }
+    }
+    SweepHooks hooks{};
+    for (int a = 0; a < 3; ++a) {
+        hooks.mon_lo[a] = mon.lo[a];
+        hooks.mon_n[a] = mon.n[a];
+        hooks.des_lo[a] = des.lo[a];
+        hooks.des_n[a] = des.n[a];
+    }
+    hooks.comp = spec->mon_comp;
+    hooks.omega = spec->omega;
+    hooks.dt = ctx->cfg.dt;
+    hooks.F = w.F;
+    hooks.hist = w.hist;
+    hooks.back = w.back;
+    float* home[6];  // the arrays the state starts and ends in
+    for (int c = 0; c < 6; ++c) home[c] = ctx->field[c];
     const double dt = ctx->cfg.dt;
     auto phase = [&](int64_t n, double* cr, double* ci) {
         const double th = spec->omega * (double)n * dt;
@@ -375,7 +428,15 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
     // ---- forward run with the monitor transform and the checkpoints
     if ((e = hipMemsetAsync(w.F, 0, 2 * (size_t)nmon * sizeof(double), st)) != hipSuccess)
         return hip_fail(ctx, e, "adjoint: clear transform");
-    for (int64_t n = 1; n <= N; ++n) {
+    for (int64_t m = 0; swept && m < nseg; ++m) {
+        const int64_t n0 = m * S, len = std::min<int64_t>(S, N - n0);
+        const bool last = m == nseg - 1;
+        if (!last && (e = copy_state(w.ckpt + (size_t)m * 6 * nc, true)) != hipSuccess)
+            return hip_fail(ctx, e, "adjoint: checkpoint");
+        int rc = sweep_forward(ctx, hooks, n0, len, last, 0);
+        if (rc) return rc;
+    }
+    for (int64_t n = 1; n <= N && !swept; ++n) {
         if (n - 1 < last0) {
             if ((n - 1) % S == 0 && (e = copy_state(w.ckpt + (size_t)((n - 1) / S) * 6 * nc, true)) != hipSuccess)
                 return hip_fail(ctx, e, "adjoint: checkpoint");
@@ -405,6 +466,12 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
     // ---- reverse sweep, one checkpointed segment at a time
     float* lE[3] = {w.lam, w.lam + nc, w.lam + 2 * nc};
     float* lH[3] = {w.lam + 3 * nc, w.lam + 4 * nc, w.lam + 5 * nc};
+    float* lam[6];
+    float* lam2[6];
+    for (int c = 0; c < 6; ++c) {
+        lam[c] = w.lam + c * nc;
+        lam2[c] = swept ? w.lam + (6 + c) * nc : nullptr;
+    }
     if ((e = hipMemsetAsync(w.lam, 0, 6 * nc * sizeof(float), st)) != hipSuccess ||
         (e = hipMemsetAsync(w.g, 0, nrec * (size_t)ndes * sizeof(double), st)) != hipSuccess)
         return hip_fail(ctx, e, "adjoint: clear");
@@ -421,6 +488,30 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
             if ((e = copy_state(w.ckpt + (size_t)m * 6 * nc, false)) != hipSuccess)
                 return hip_fail(ctx, e, "adjoint: restore checkpoint");
             ctx->step_count = s0 + n0;
+        }
+        if (swept) {
+            int rc = FDTD_OK;
+            if (m < nseg - 1) {
+                SweepHooks again = hooks;
+                again.mon_n[0] = 0;  // the monitor has its samples
+                rc = sweep_forward(ctx, again, n0, len - 1, true, 0);
+                hipLaunchKernelGGL((lossy ? adj_curl_box_kernel<true> : adj_curl_box_kernel<false>),
+                                   dim3(box_grid(ndes)), dim3(256), 0, st, ctx->field[3], ctx->field[4],
+                                   ctx->field[5], ctx->field[0], ctx->field[1], ctx->field[2], des, ctx->nx,
+                                   ctx->ny, ctx->nz, w.hist + (size_t)(len - 1) * nrec * ndes);
+            }
+            for (int64_t left = len; left > 0 && !rc;) {
+                const int64_t k = std::min(run, left);
+                rc = sweep_reverse(ctx, hooks, lam, lam2, n0 + left - k, k);
+                hipLaunchKernelGGL((lossy ? adj_grad_run_kernel<true> : adj_grad_run_kernel<false>),
+                                   dim3(box_grid((long long)nrec * ndes)), dim3(256), 0, st, (const float*)w.back,
+                                   (const float*)(w.hist + (size_t)(left - 1) * nrec * ndes), ndes, (int)k, w.g);
+                left -= k;
+            }
+            if (rc) return rc;
+            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(ctx, e, "launch(adjoint sweep)");
+            if (m < nseg - 1) recomputed += len - 1;
+            continue;
         }
         for (int64_t l = 0; m < nseg - 1 && l < len; ++l) {
             // CH(H^{n-1/2}) (and E^{n-1}) for step n = n0 + l + 1, before that step runs
@@ -459,6 +550,14 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
     if (nckpt && (e = copy_state(w.ckpt + (size_t)(nseg - 1) * 6 * nc, false)) != hipSuccess)
         return hip_fail(ctx, e, "adjoint: restore final state");
     ctx->step_count = s0 + N;
+    if (ctx->field[0] != home[0]) {
+        // an odd number of passes: back into the arrays it started from
+        for (int c = 0; c < 6 && e == hipSuccess; ++c) {
+            e = hipMemcpyAsync(home[c], ctx->field[c], nc * sizeof(float), hipMemcpyDeviceToDevice, st);
+            std::swap(ctx->field[c], ctx->alt[c]);
+        }
+        if (e != hipSuccess) return hip_fail(ctx, e, "adjoint: final state");
+    }
     float* dst = where == FDTD_DEVICE ? grad_eps : w.out;
     hipLaunchKernelGGL((lossy ? adj_eps_kernel<true> : adj_eps_kernel<false>), dim3(box_grid(ndes)),
                        dim3(256), 0, st, (const double*)w.g, ctx->coef[0], ctx->coef[1], ctx->coef[2],

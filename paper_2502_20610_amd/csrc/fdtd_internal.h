@@ -150,6 +150,27 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);
 // The longest pass, the blocks and the tiles of the last sweep of the context.
 void sweep_shape(const fdtd_ctx* ctx, int* steps, int* blocks, int* tiles);
 void sweep_release(fdtd_ctx* ctx);
+
+// What the adjoint of a monitor objective adds to a sweep (adjoint.hip): the
+// monitor transform F and the design-box history of the forward run, the
+// monitor samples and the gradient sums of the reverse one.
+struct SweepHooks {
+    int mon_lo[3], mon_n[3], des_lo[3], des_n[3];
+    int comp;          // monitored E component
+    double omega, dt;
+    double* F;         // re, im per monitor cell
+    float* hist;       // one record of (3 or 6) x design cells per step, or null
+    float* back;       // reverse run: one record of 3 x design cells per step
+};
+// Whether the adjoint can sweep this grid (and the second field set is there).
+bool sweep_hooked_ready(fdtd_ctx* ctx);
+// Forward steps n0 + 1 .. n0 + n of the run; `record` writes step n0 + 1 + l
+// to record first + l of the history.
+int sweep_forward(fdtd_ctx* ctx, const SweepHooks& h, int64_t n0, int64_t n, bool record, int64_t first);
+// Reverse steps n0 + n .. n0 + 1 of the adjoint state lam (into lam2 and
+// back: the pointers trade places with every pass); the adjoint E of step
+// n0 + n - l goes to record l of h.back.
+int sweep_reverse(fdtd_ctx* ctx, const SweepHooks& h, float* lam[6], float* lam2[6], int64_t n0, int64_t n);
 // Free the captured step graph and its counter (plain.hip).
 void release_step_graph_exec(StepGraph* g);
 void release_step_graph(fdtd_ctx* ctx);

@@ -31,6 +31,8 @@
 // of planes in flight are parked in LDS), stores bypass the caches, and blocks
 // of one XCD are kept in step (below) so that the halos of neighbouring tiles
 // meet in its L2.
+#include <math.h>
+
 #include <algorithm>
 #include <new>
 
@@ -44,7 +46,48 @@ constexpr int kPaceGroup = 32;   // blocks an XCD runs at once (one per CU)
 constexpr int kPacePlanes = 4;   // planes between two progress marks
 constexpr unsigned kDropped = 0x80000000u;  // a buffer offset past every plane: the access is dropped
 
+constexpr int kMaxT = 5;         // steps of a pass
+
 enum { kArrays = 0, kLossy = 1, kTable = 2, kLossyTable = 3 };
+// What a pass computes: the update; the update with what the forward run of
+// the adjoint takes from it (monitor transform, design-box history); the
+// transposed half-steps of the reverse run,
+//   lE = A (.) lE - cH CH(lH),  lH += CE(cE (.) lE),
+// with the monitor samples of the step added to lE and lE recorded over the
+// design box, or without either.  A block that meets neither box runs the
+// plain form of its pass.
+enum { kUpdate = 0, kForward = 1, kReverse = 2, kTransposed = 3 };
+
+// Level l of a pass is step n + l (forward) or n - l (reverse).  A cell of the
+// design box, and in the forward run of the monitor box, belongs to the lane
+// that stores it; it adds to the transform once per level, in the order of the
+// levels, by adds that return nothing.  The records only leave the kernel, so
+// no level waits for memory.
+struct HookArgs {
+    int dlo[3], dn[3], mlo[3], mn[3];
+    int comp;
+    double cr[kMaxT], ci[kMaxT];  // exp(-i omega n dt) of the levels
+    double* F;
+    float* hist;       // the record of level 0 (null: none)
+    long long stride;  // from the record of a level to that of the next
+};
+
+template <int T, int R, int W, int MODE>
+struct Lds {
+    static constexpr bool TAB = MODE == kTable || MODE == kLossyTable;
+    static constexpr int kList = 64;  // sources a block keeps at hand
+    float2 hx0[2][W][64];                  // (Hx, Hz) of a wavefront's top row, level 0
+    float2 hx[T > 1 ? T - 1 : 1][W][64];   // and levels 1 ..
+    float2 ex[2][T][W][64];
+    float4 tab[TAB ? kMaxMaterials : 1];
+    float4 tabA[MODE == kLossyTable ? kMaxMaterials : 1];
+    unsigned ids[TAB ? T : 1][(R + 3) / 4][64 * W];
+    // a source: its plane and byte offset in it; bits 0..1 its component,
+    // bit 8 + l whether it has a sample for level l; the samples
+    int plane[kList], cell[kList], what[kList];
+    float sample[T][kList];
+    int nlist;
+};
 
 struct SweepArgs {
     const float* in[6];
@@ -92,32 +135,21 @@ __device__ __forceinline__ int wrap(int v, int n)
     return m < 0 ? m + n : m;
 }
 
-template <int T, int R, int W, int MODE, bool WHOLE>
-__device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nblocks)
+template <int T, int R, int W, int MODE, bool WHOLE, int HOOK>
+__device__ __forceinline__ void sweep_tile(const SweepArgs& A, const HookArgs& K,
+                                           Lds<T, R, W, MODE>& S, int xcd, int slot, int per_xcd)
 {
     static_assert(W * R > 2 * T && 64 > 2 * T, "the tile keeps at least one cell");
+    static_assert(HOOK == kUpdate || MODE == kArrays || MODE == kLossy, "the hooks read the arrays");
+    constexpr bool BOXES = HOOK == kForward || HOOK == kReverse;
+    constexpr bool BACK = HOOK == kReverse || HOOK == kTransposed;
     constexpr int NS = T + 2;
     constexpr bool TAB = MODE == kTable || MODE == kLossyTable;
     constexpr bool LOSSY = MODE == kLossy || MODE == kLossyTable;
     constexpr int NC = LOSSY ? 6 : 3;  // coefficients per cell
     constexpr int NP = (R + 3) / 4;    // words of packed indices per plane and lane
-    constexpr int kList = 64;          // sources a block keeps at hand
-    __shared__ float2 hx_[T == 1 ? 2 : 1][T][W][64];
-    __shared__ float2 ex_[2][T][W][64];
-    __shared__ float4 tab_[TAB ? kMaxMaterials : 1];
-    __shared__ float4 tabA_[MODE == kLossyTable ? kMaxMaterials : 1];
-    __shared__ unsigned ids_[TAB ? T : 1][NP][64 * W];
-    __shared__ int list_[kList];
-    __shared__ int nlist_;
-    // launch order is dealt round the XCDs; tiles are contiguous per XCD
-    const int per_xcd = nblocks / kXCD, xcd = block % kXCD, slot = block / kXCD;
+    constexpr int kList = Lds<T, R, W, MODE>::kList;
     const int tile = xcd * per_xcd + slot;
-    if (A.pace_next) {
-        const int each = (A.pace_words + nblocks - 1) / nblocks;
-        for (int q = threadIdx.x; q < each; q += 64 * W)
-            if (block * each + q < A.pace_words) A.pace_next[block * each + q] = 0u;
-    }
-    if (tile >= A.ntiles) return;  // whole block
     const int tz = tile % A.gz, ty = (tile / A.gz) % A.gy, tx = tile / (A.gz * A.gy);
     const int L = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -125,16 +157,41 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
     const int x0 = tx * A.xchunk, x1 = min(A.nx, x0 + A.xchunk);
     const int nit = x1 - x0 + 2 * T;
     const int k = wrap(k0 + L, A.nz);
-    const bool kown = WHOLE || (L >= T && L < 64 - T && k0 + L < A.nz);
-    unsigned off[R];            // byte offset of the lane's cell in a plane
-    unsigned long long own[R];  // lanes that store row r
+    // the lanes and rows that the tile stores
+    const unsigned long long kown = __ballot(WHOLE || (L >= T && L < 64 - T && k0 + L < A.nz));
+    auto jown = [&](int r) { return w * R + r >= T && w * R + r < W * R - T && j0 + w * R + r < A.ny; };
+    // Byte offsets of the lane's cells in a plane.  The tile that fills the
+    // registers adds a scalar offset per row to one of the lane instead (with
+    // an offset per row it spills, and a spill waits for the planes in flight:
+    // 256^3 74 -> 93 us per step; where there is room the scalar offsets cost
+    // up to 8%).
+    constexpr bool SOFF = T == 5 && R == 3;
+    unsigned vo[SOFF ? 1 : R], so[SOFF ? R : 1];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int rr = w * R + r;
-        off[r] = ((unsigned)wrap(j0 + rr, A.ny) * (unsigned)A.nz + (unsigned)k) * 4u;
-        own[r] = __ballot(kown && rr >= T && rr < W * R - T && j0 + rr < A.ny);
+        const unsigned row = (unsigned)wrap(j0 + rr, A.ny) * (unsigned)A.nz * 4u;
+        vo[SOFF ? 0 : r] = (unsigned)k * 4u + (SOFF ? 0u : row);
+        so[SOFF ? r : 0] = SOFF ? row : 0u;
     }
     const unsigned pbytes = (unsigned)A.ny * (unsigned)A.nz * 4u;
+    // the lane's cells in the design and monitor boxes: index within a plane of
+    // the box, or -1 (not there; the design box and the forward run's monitor
+    // count a cell where it is stored, the reverse run's monitor samples go to
+    // every copy of a cell)
+    constexpr int BR = BOXES ? R : 1;
+    int qd[BR], qm[BR];
+    if (BOXES) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int j = wrap(j0 + w * R + r, A.ny), jd = j - K.dlo[1], kd = k - K.dlo[2];
+            const int jm = j - K.mlo[1], km = k - K.mlo[2];
+            const bool mine = (kown >> L & 1) && jown(r), meets = mine || HOOK == kReverse;
+            qd[r % BR] = mine && jd >= 0 && jd < K.dn[1] && kd >= 0 && kd < K.dn[2] ? jd * K.dn[2] + kd : -1;
+            qm[r % BR] = meets && jm >= 0 && jm < K.mn[1] && km >= 0 && km < K.mn[2] ? jm * K.mn[2] + km : -1;
+        }
+    }
+    const long long ndes = BOXES ? (long long)K.dn[0] * K.dn[1] * K.dn[2] : 0;
     constexpr int CS = TAB ? 1 : NS, CR = TAB ? 1 : R, CC = TAB ? 1 : NC;
     float E[NS][R][3], H[NS][R][3], C[CS][CR][CC];
     unsigned ci[R];
@@ -155,30 +212,30 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
         const char* p = (const char*)base + (unsigned long long)(unsigned)plane * bytes;
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), (short)0, (int)bytes, 0x00020000);
     };
-    auto ld = [&](const void* base, int plane, unsigned o) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(base, plane, pbytes), (int)o, 0, 0));
+    auto ld = [&](const void* base, int plane, int r) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(base, plane, pbytes), (int)vo[SOFF ? 0 : r], (int)so[SOFF ? r : 0], 0));
     };
     int pin = wrap(x0 - T, A.nx);  // grid plane of the next load
     auto load = [&](int s) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
 #pragma unroll
-            for (int r = 0; r < R; ++r) H[s][r][c] = ld(A.in[3 + c], pin, off[r]);
+            for (int r = 0; r < R; ++r) H[s][r][c] = ld(A.in[3 + c], pin, r);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
 #pragma unroll
-            for (int r = 0; r < R; ++r) E[s][r][c] = ld(A.in[c], pin, off[r]);
+            for (int r = 0; r < R; ++r) E[s][r][c] = ld(A.in[c], pin, r);
         if (TAB) {
             const auto ri = rsrc(A.id, pin, pbytes >> 2);
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                ci[r] = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(ri, (int)(off[r] >> 2), 0, 0);
+                ci[r] = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(ri, (int)(vo[SOFF ? 0 : r] >> 2), (int)(so[SOFF ? r : 0] >> 2), 0);
         } else {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    C[s % CS][r % CR][c % CC] = ld(c < 3 ? A.cE[c % 3] : A.ca[c % 3], pin, off[r]);
+                    C[s % CS][r % CR][c % CC] = ld(c < 3 ? A.cE[c % 3] : A.ca[c % 3], pin, r);
         }
         pin = pin + 1 == A.nx ? 0 : pin + 1;
     };
@@ -186,13 +243,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
     if (TAB) {
         for (int q = threadIdx.x; q < A.ntab; q += 64 * W) {
             const float* t = A.tab + q * NC;
-            tab_[q] = make_float4(t[0], t[1], t[2], 0.f);
-            if (MODE == kLossyTable) tabA_[q] = make_float4(t[NC - 3], t[NC - 2], t[NC - 1], 0.f);
+            S.tab[q] = make_float4(t[0], t[1], t[2], 0.f);
+            if (MODE == kLossyTable) S.tabA[q] = make_float4(t[NC - 3], t[NC - 2], t[NC - 1], 0.f);
         }
 #pragma unroll
         for (int d = 0; d < T; ++d)
 #pragma unroll
-            for (int q = 0; q < NP; ++q) ids_[d][q][threadIdx.x] = 0u;
+            for (int q = 0; q < NP; ++q) S.ids[d][q][threadIdx.x] = 0u;
     }
     // the sources this block meets, in table order (several on one cell add up
     // in the same order as in any other scheme)
@@ -210,17 +267,29 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
                 }
                 const unsigned long long m = __ballot(hit);
                 const int at = n + __popcll(m & ((1ull << L) - 1));
-                if (hit && at < kList) list_[at] = q;
+                if (hit && at < kList) {
+                    const DevSource s = A.src[q];
+                    int what = s.comp;
+#pragma unroll
+                    for (int l = 0; l < T; ++l) {
+                        const long long i = A.step + l - s.first;
+                        if (i < 0 || i >= s.len) continue;
+                        what |= 256 << l;
+                        S.sample[l][at] = s.wave[i];
+                    }
+                    S.plane[at] = s.i;
+                    S.cell[at] = (int)(((unsigned)s.j * (unsigned)A.nz + (unsigned)s.k) * 4u);
+                    S.what[at] = what;
+                }
                 n += __popcll(m);
             }
-            if (L == 0) nlist_ = n;
+            if (L == 0) S.nlist = n;
         }
         __syncthreads();
-        nhit = __builtin_amdgcn_readfirstlane(nlist_);
+        nhit = __builtin_amdgcn_readfirstlane(S.nlist);
     }
     // lane e of every wavefront holds the plane of entry e
-    int lsi = -1;
-    if (nhit > 0 && nhit <= kList && L < nhit) lsi = A.src[list_[L]].i;
+    const int lsi = nhit <= kList && L < nhit ? S.plane[L] : -1;
     // Blocks of one XCD in step: each marks its progress every few planes, and
     // one that is ahead of the slowest of its group rests a little.  Nothing
     // depends on it: a mark is read once, never waited for.
@@ -245,7 +314,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
 #pragma unroll
                     for (int r = 1; r < 4; ++r)
                         if (4 * q + r < R) pk[q] |= ci[4 * q + r < R ? 4 * q + r : 0] << (8 * r);
-                    ids_[ring][q][threadIdx.x] = pk[q];
+                    S.ids[ring][q][threadIdx.x] = pk[q];
                 }
             }
             if (it + 1 < nit) load((u + 1) % NS);
@@ -259,36 +328,61 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
                     if (it >= 2 * P - 1) seen = __hip_atomic_load(p - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
-            hx_[T == 1 ? par : 0][0][w][L] = make_float2(H[u][R - 1][0], H[u][R - 1][2]);
+            S.hx0[par][w][L] = make_float2(H[u][R - 1][0], H[u][R - 1][2]);
 #pragma unroll
             for (int l = 0; l < T; ++l) {
                 const int s0 = (u - l + NS) % NS, s1 = (u - l - 1 + NS) % NS;
-                // until it = 2l no stored value depends on level l
+                // Until it = 2l no stored value depends on level l.  (An
+                // iteration may then have one barrier alone: what level 0 and
+                // the E rows exchange alternates between two buffers.)
                 if (it < 2 * l) break;
                 if (TAB && l > 0) {
                     const int q0 = ring - l < 0 ? ring - l + T : ring - l;
 #pragma unroll
-                    for (int q = 0; q < NP; ++q) pk[q] = ids_[q0][q][threadIdx.x];
+                    for (int q = 0; q < NP; ++q) pk[q] = S.ids[q0][q][threadIdx.x];
                 }
                 lds_barrier();
-                const float2 hl = hx_[T == 1 ? par : 0][l][w == 0 ? 0 : w - 1][L];
-                const float2 eu = ex_[par ^ 1][l][w == W - 1 ? w : w + 1][L];
+                const float2 hl = l == 0 ? S.hx0[par][w == 0 ? 0 : w - 1][L] : S.hx[l > 0 ? l - 1 : 0][w == 0 ? 0 : w - 1][L];
+                const float2 eu = S.ex[par ^ 1][l][w == W - 1 ? w : w + 1][L];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const float hx = H[s0][r][0], hy = H[s0][r][1], hz = H[s0][r][2];
                     const float hx_jm = r ? H[s0][r - 1][0] : hl.x, hz_jm = r ? H[s0][r - 1][2] : hl.y;
                     const float hx_km = from_below<WHOLE>(hx), hy_km = from_below<WHOLE>(hy);
                     const float hy_im = H[s1][r][1], hz_im = H[s1][r][2];
+                    if (HOOK == kForward && K.hist) {
+                        const int p = it - l, id = x0 + p - T - K.dlo[0];
+                        if (p >= T && p < nit - T && id >= 0 && id < K.dn[0] && qd[r % BR] >= 0) {
+                            float* o = K.hist + l * K.stride + (long long)id * K.dn[1] * K.dn[2] + qd[r % BR];
+                            o[0] = (hz - hz_jm) - (hy - hy_km);
+                            o[ndes] = (hx - hx_km) - (hz - hz_im);
+                            o[2 * ndes] = (hy - hy_im) - (hx - hx_jm);
+                            if (LOSSY) {
+                                o[3 * ndes] = E[s0][r][0];
+                                o[4 * ndes] = E[s0][r][1];
+                                o[5 * ndes] = E[s0][r][2];
+                            }
+                        }
+                    }
+                    if (BACK) {
+                        const float* cc = C[s0 % CS][r % CR];
+                        const float dx = (hz - hz_jm) - (hy - hy_km), dy = (hx - hx_km) - (hz - hz_im),
+                                    dz = (hy - hy_im) - (hx - hx_jm);
+                        E[s0][r][0] = (LOSSY ? cc[3 % CC] * E[s0][r][0] : E[s0][r][0]) - A.cH * dx;
+                        E[s0][r][1] = (LOSSY ? cc[4 % CC] * E[s0][r][1] : E[s0][r][1]) - A.cH * dy;
+                        E[s0][r][2] = (LOSSY ? cc[5 % CC] * E[s0][r][2] : E[s0][r][2]) - A.cH * dz;
+                        continue;
+                    }
                     float cx, cy, cz;
                     float ex = E[s0][r][0], ey = E[s0][r][1], ez = E[s0][r][2];
                     if (TAB) {
                         const unsigned id = pk[r / 4] >> (8 * (r % 4)) & 255u;
-                        const float4 t = tab_[id];
+                        const float4 t = S.tab[id];
                         cx = t.x;
                         cy = t.y;
                         cz = t.z;
                         if (MODE == kLossyTable) {
-                            const float4 a = tabA_[id];
+                            const float4 a = S.tabA[id];
                             ex = a.x * ex;
                             ey = a.y * ey;
                             ez = a.z * ez;
@@ -310,18 +404,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
                 }
                 if (nhit > 0) {
                     const int pl = wrap(pe - l, A.nx);
-                    auto add = [&](int q) {
-                        const DevSource s = A.src[q];
-                        const long long m = A.step + l - s.first;
-                        if (s.i != pl || m < 0 || m >= s.len) return;
-                        const float v = s.wave[m];
-                        const unsigned cell = ((unsigned)s.j * (unsigned)A.nz + (unsigned)s.k) * 4u;
+                    auto add = [&](int c, unsigned cell, float v) {
 #pragma unroll
                         for (int r = 0; r < R; ++r)
-                            if (off[r] == cell) {
-                                E[s0][r][0] = s.comp == 0 ? E[s0][r][0] + v : E[s0][r][0];
-                                E[s0][r][1] = s.comp == 1 ? E[s0][r][1] + v : E[s0][r][1];
-                                E[s0][r][2] = s.comp == 2 ? E[s0][r][2] + v : E[s0][r][2];
+                            if (SOFF ? vo[0] == cell - so[SOFF ? r : 0] : vo[SOFF ? 0 : r] == cell) {
+                                E[s0][r][0] = c == 0 ? E[s0][r][0] + v : E[s0][r][0];
+                                E[s0][r][1] = c == 1 ? E[s0][r][1] + v : E[s0][r][1];
+                                E[s0][r][2] = c == 2 ? E[s0][r][2] + v : E[s0][r][2];
                             }
                     };
                     if (nhit <= kList) {
@@ -329,13 +418,71 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
                         while (m) {
                             const int e = __ffsll((long long)m) - 1;
                             m &= m - 1;
-                            add(__builtin_amdgcn_readfirstlane(list_[e]));
+                            const int what = S.what[e];
+                            if (what >> (8 + l) & 1) add(what & 3, (unsigned)S.cell[e], S.sample[l][e]);
                         }
                     } else {
-                        for (int q = 0; q < A.nsrc; ++q) add(q);
+                        // too many to keep: the whole table
+                        for (int q = 0; q < A.nsrc; ++q) {
+                            const DevSource s = A.src[q];
+                            const long long i = A.step + l - s.first;
+                            if (s.i == pl && i >= 0 && i < s.len)
+                                add(s.comp, ((unsigned)s.j * (unsigned)A.nz + (unsigned)s.k) * 4u, s.wave[i]);
+                        }
                     }
                 }
-                ex_[par][l][w][L] = make_float2(E[s0][0][0], E[s0][0][2]);
+                if (BOXES) {
+                    const int p = it - l, im = wrap(pe - l, A.nx) - K.mlo[0], id = x0 + p - T - K.dlo[0];
+                    const bool mine = p >= T && p < nit - T;
+                    if ((mine || HOOK == kReverse) && im >= 0 && im < K.mn[0])
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            if (qm[r % BR] < 0) continue;
+                            double* f = K.F + 2 * ((long long)im * K.mn[1] * K.mn[2] + qm[r % BR]);
+                            if (HOOK == kForward) {
+                                const double e = (double)(K.comp == 0 ? E[s0][r][0] : K.comp == 1 ? E[s0][r][1] : E[s0][r][2]);
+                                unsafeAtomicAdd(f, e * K.cr[l]);
+                                unsafeAtomicAdd(f + 1, e * K.ci[l]);
+                            } else {
+                                const double v = 2.0 * (f[0] * K.cr[l] + f[1] * K.ci[l]);
+#pragma unroll
+                                for (int c = 0; c < 3; ++c)
+                                    E[s0][r][c] = K.comp == c ? (float)((double)E[s0][r][c] + v) : E[s0][r][c];
+                            }
+                        }
+                    if (HOOK == kReverse && mine && id >= 0 && id < K.dn[0])
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            if (qd[r % BR] < 0) continue;
+                            float* o = K.hist + l * K.stride + (long long)id * K.dn[1] * K.dn[2] + qd[r % BR];
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) o[c * ndes] = E[s0][r][c];
+                        }
+                }
+                if (BACK) {
+                    // H += CE(w), w = cE (.) E: the neighbours exchange w
+                    const float* c0 = C[s0 % CS][0];
+                    S.ex[par][l][w][L] = make_float2(c0[0] * E[s0][0][0], c0[2 % CC] * E[s0][0][2]);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        constexpr int last = R - 1;
+                        const int rn = r < last ? r + 1 : r;
+                        const float* c1 = C[s1 % CS][r % CR];
+                        const float* cn = C[s1 % CS][rn % CR];
+                        const float* cp = C[s0 % CS][r % CR];
+                        const float wx = c1[0] * E[s1][r][0], wy = c1[1 % CC] * E[s1][r][1], wz = c1[2 % CC] * E[s1][r][2];
+                        const float wx_jp = r < last ? cn[0] * E[s1][rn][0] : eu.x;
+                        const float wz_jp = r < last ? cn[2 % CC] * E[s1][rn][2] : eu.y;
+                        const float wy_kp = from_above<WHOLE>(wy), wx_kp = from_above<WHOLE>(wx);
+                        const float wy_ip = cp[1 % CC] * E[s0][r][1], wz_ip = cp[2 % CC] * E[s0][r][2];
+                        H[s1][r][0] += (wz_jp - wz) - (wy_kp - wy);
+                        H[s1][r][1] += (wx_kp - wx) - (wz_ip - wz);
+                        H[s1][r][2] += (wy_ip - wy) - (wx_jp - wx);
+                    }
+                    if (l + 1 < T) S.hx[l + 1 < T ? l : 0][w][L] = make_float2(H[s1][R - 1][0], H[s1][R - 1][2]);
+                    continue;
+                }
+                S.ex[par][l][w][L] = make_float2(E[s0][0][0], E[s0][0][2]);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const float ex = E[s1][r][0], ey = E[s1][r][1], ez = E[s1][r][2];
@@ -347,20 +494,20 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
                     H[s1][r][1] = (H[s1][r][1] - A.cH * (ex_kp - ex)) + A.cH * (ez_ip - ez);
                     H[s1][r][2] = (H[s1][r][2] - A.cH * (ey_ip - ey)) + A.cH * (ex_jp - ex);
                 }
-                if (l + 1 < T) hx_[0][l + 1 < T ? l + 1 : 0][w][L] = make_float2(H[s1][R - 1][0], H[s1][R - 1][2]);
+                if (l + 1 < T) S.hx[l + 1 < T ? l : 0][w][L] = make_float2(H[s1][R - 1][0], H[s1][R - 1][2]);
             }
             if (it >= 2 * T) {
                 const int s = (u - T + NS) % NS;
                 const int plane = x0 + it - 2 * T;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const unsigned so = __builtin_amdgcn_inverse_ballot_w64(own[r]) ? off[r] : kDropped;
+                    const unsigned sr = __builtin_amdgcn_inverse_ballot_w64(jown(r) ? kown : 0ull) ? vo[SOFF ? 0 : r] : kDropped;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, E[s][r][c]),
-                                                              rsrc(A.out[c], plane, pbytes), (int)so, 0, 2);
+                                                              rsrc(A.out[c], plane, pbytes), (int)sr, (int)so[SOFF ? r : 0], 2);
                         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, H[s][r][c]),
-                                                              rsrc(A.out[3 + c], plane, pbytes), (int)so, 0, 2);
+                                                              rsrc(A.out[3 + c], plane, pbytes), (int)sr, (int)so[SOFF ? r : 0], 2);
                     }
                 }
             }
@@ -370,36 +517,88 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& A, int block, int nb
     }
 }
 
+// Whether [start, start + len) meets [lo, lo + n), indices modulo N.
+__device__ __forceinline__ bool meets(int start, int len, int lo, int n, int N)
+{
+    return n > 0 && (wrap(start - lo, N) < n || wrap(lo - start, N) < len);
+}
+
+// The block's place: launch order is dealt round the XCDs, tiles are
+// contiguous per XCD.  Clears its share of the next pass's progress marks.
+// False: no tile for it.
+__device__ __forceinline__ bool place(const SweepArgs& A, int& xcd, int& slot, int& per_xcd)
+{
+    per_xcd = (int)gridDim.x / kXCD;
+    xcd = (int)blockIdx.x % kXCD;
+    slot = (int)blockIdx.x / kXCD;
+    if (A.pace_next) {
+        const int each = (A.pace_words + (int)gridDim.x - 1) / (int)gridDim.x;
+        for (int q = threadIdx.x; q < each; q += (int)blockDim.x)
+            if ((int)blockIdx.x * each + q < A.pace_words) A.pace_next[(int)blockIdx.x * each + q] = 0u;
+    }
+    return xcd * per_xcd + slot < A.ntiles;
+}
+
 template <int T, int R, int W, int MODE, bool WHOLE>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4))) void sweep_kernel(
     const SweepArgs A)
 {
-    sweep_tile<T, R, W, MODE, WHOLE>(A, (int)blockIdx.x, (int)gridDim.x);
+    __shared__ Lds<T, R, W, MODE> S;
+    int xcd, slot, per_xcd;
+    if (!place(A, xcd, slot, per_xcd)) return;  // whole block
+    sweep_tile<T, R, W, MODE, WHOLE, kUpdate>(A, HookArgs{}, S, xcd, slot, per_xcd);
+}
+
+template <int T, int R, int W, int MODE, int HOOK>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4))) void hooked_kernel(
+    const SweepArgs A, const HookArgs K)
+{
+    __shared__ Lds<T, R, W, MODE> S;
+    int xcd, slot, per_xcd;
+    if (!place(A, xcd, slot, per_xcd)) return;  // whole block
+    const int tile = xcd * per_xcd + slot;
+    const int k0 = tile % A.gz * (64 - 2 * T) - T, j0 = tile / A.gz % A.gy * (W * R - 2 * T) - T;
+    const int x0 = tile / (A.gz * A.gy) * A.xchunk, nit = min(A.nx, x0 + A.xchunk) - x0 + 2 * T;
+    auto box = [&](const int* lo, const int* n) {
+        return meets(x0 - T, nit, lo[0], n[0], A.nx) && meets(j0, W * R, lo[1], n[1], A.ny) && meets(k0, 64, lo[2], n[2], A.nz);
+    };
+    if (box(K.dlo, K.dn) || box(K.mlo, K.mn))
+        sweep_tile<T, R, W, MODE, false, HOOK>(A, K, S, xcd, slot, per_xcd);
+    else
+        sweep_tile<T, R, W, MODE, false, HOOK == kReverse ? kTransposed : kUpdate>(A, K, S, xcd, slot, per_xcd);
 }
 
 // Tile shapes: T steps per pass, R rows per lane, W wavefronts.
 struct Variant {
     int T, R, W, mode;
     bool whole;  // for grids whose z axis is one wavefront
-    void (*kern)(const SweepArgs);
+    int hook;
+    void (*kern)(const SweepArgs);                    // (hook kUpdate)
+    void (*hooked)(const SweepArgs, const HookArgs);  // (the others)
 };
-#define V(T, R, W, M) {T, R, W, M, false, sweep_kernel<T, R, W, M, false>}
-#define VW(T, W, M) {T, 1, W, M, true, sweep_kernel<T, 1, W, M, true>}
+#define V(T, R, W, M) {T, R, W, M, false, kUpdate, sweep_kernel<T, R, W, M, false>, nullptr}
+#define VW(T, W, M) {T, 1, W, M, true, kUpdate, sweep_kernel<T, 1, W, M, true>, nullptr}
 #define VW4(W, M) VW(1, W, M), VW(2, W, M), VW(3, W, M), VW(4, W, M)
+#define VH(T, R, W, M) {T, R, W, M, false, kForward, nullptr, hooked_kernel<T, R, W, M, kForward>}, \
+    {T, R, W, M, false, kReverse, nullptr, hooked_kernel<T, R, W, M, kReverse>}
 #define V2(R, W, M) V(1, R, W, M), V(2, R, W, M)
 #define V3(R, W, M) V2(R, W, M), V(3, R, W, M)
 #define V4(R, W, M) V3(R, W, M), V(4, R, W, M)
 #define V5(R, W, M) V4(R, W, M), V(5, R, W, M)
 const Variant kVariants[] = {
-    V5(2, 16, kTable),      V4(1, 16, kTable),
-    V5(2, 16, kLossyTable), V4(1, 16, kLossyTable),
+    V5(3, 12, kTable),      V4(2, 16, kTable),     V4(1, 16, kTable),
+    V4(3, 12, kLossyTable), V5(2, 16, kLossyTable), V4(1, 16, kLossyTable),
     V4(4, 8, kArrays),      V3(2, 16, kArrays), V4(1, 16, kArrays),
     V3(3, 8, kLossy),       V2(2, 16, kLossy), V4(1, 16, kLossy),
+    VH(1, 1, 16, kArrays), VH(2, 1, 16, kArrays), VH(3, 1, 16, kArrays), VH(4, 1, 16, kArrays),
+    VH(2, 4, 8, kArrays), VH(3, 4, 8, kArrays),
+    VH(1, 1, 16, kLossy), VH(2, 1, 16, kLossy), VH(3, 1, 16, kLossy), VH(2, 3, 8, kLossy), VH(3, 3, 8, kLossy),
     VW4(16, kTable),        VW4(16, kArrays),    VW4(16, kLossyTable), VW4(16, kLossy),
 };
 #undef V
 #undef VW
 #undef VW4
+#undef VH
 #undef V2
 #undef V3
 #undef V4
@@ -414,7 +613,6 @@ struct Pass {
     double us = 1e300;  // estimated
 };
 
-constexpr int kMaxT = 5;
 constexpr double kCacheBytes = 256e6;  // Infinity Cache
 
 int mode_of(const fdtd_ctx* c)
@@ -423,36 +621,40 @@ int mode_of(const fdtd_ctx* c)
     return c->ca[0] ? (tab ? kLossyTable : kLossy) : (tab ? kTable : kArrays);
 }
 
-// The fastest pass of T steps by a model of the time of one iteration of a
-// block, fitted to measured passes from 64^3 to 1024 x 1024 x 512: with all
-// CUs busy a block takes 0.5 us + 0.2 us per level + 0.125 us per level and 8
-// rows, or the time its loads and stores take at 17.6 KB/us per CU (4.5 TB/s
-// in all; 2.2 times that where the state sits in the Infinity Cache),
-// whichever is longer; a chunk's 2T extra planes and the last round of blocks
-// count in full.
-Pass plan_pass(const fdtd_ctx* c, int mode, int T, int cus)
+// The best pass of T steps by a model of a block's time, fitted to passes
+// measured from 32^3 to 1024 x 1024 x 512 (within 20%): 3 us for the launch;
+// per iteration 0.45 us and, for each level that runs, 0.11 us + 0.29 us per 16
+// rows; or the time the loads and stores of the iterations take at 17.6 KB/us
+// per CU (4.5 TB/s in all; 2.2 times that where everything sits in the
+// Infinity Cache), if that is longer; the last round of blocks counts in full.
+// Where a pass does not fill the device, fewer blocks leave room for another
+// context's (three contexts in turn, 48^3: chunks of one plane 3.3 us per step,
+// of two 2.1, and 4.4 for either alone): the blocks of a full device count 0.6 more.
+Pass plan_pass(const fdtd_ctx* c, int mode, int hook, int T, int cus)
 {
     Pass best;
     const int in_bytes = 24 + (mode == kArrays ? 12 : mode == kLossy ? 24 : 1);
-    const bool cached = 24.0 * (double)c->ncell <= kCacheBytes;
+    const bool cached = (24.0 + in_bytes) * (double)c->ncell <= kCacheBytes;
     for (const Variant& v : kVariants) {
-        if (v.T != T || v.mode != mode || (v.whole && c->nz != 64)) continue;
+        if (v.T != T || v.mode != mode || v.hook != hook || (v.whole && c->nz != 64)) continue;
         const int rows = v.R * v.W, vz = v.whole ? 64 : 64 - 2 * T, vy = rows - 2 * T;
         Pass p;
         p.v = &v;
         p.gz = (c->nz + vz - 1) / vz;
         p.gy = (c->ny + vy - 1) / vy;
         const long long base = (long long)p.gz * p.gy;
-        const double compute = 0.5 + T * (0.2 + rows / 64.0);
+        const double level = 0.11 + 0.29 * rows / 16.0;
         const double memory = (rows * 64.0 * in_bytes + vy * vz * 24.0) / (cached ? 2.2 * 17600.0 : 17600.0);
-        const double iter = std::max(compute, memory);
         int last = 0;
         for (int q = 1; q <= std::min(c->nx, 1024); ++q) {
             const int xc = (c->nx + q - 1) / q;
             if (xc == last) continue;
             last = xc;
             const long long nt = base * ((c->nx + xc - 1) / xc);
-            const double us = (double)((nt + cus - 1) / cus) * (xc + 2 * T + 1) * iter + 5.0;
+            // (level l starts at iteration 2l)
+            const double compute = 0.45 * (xc + 2 * T) + level * (T * (T + 1) + (double)xc * T);
+            const double us = ((double)((nt + cus - 1) / cus) * std::max(compute, memory * (xc + 2 * T)) + 3.0) *
+                              (1.0 + 0.6 * std::min(1.0, (double)nt / cus));
             if (us < p.us) {
                 p.us = us;
                 p.xchunk = xc;
@@ -470,7 +672,9 @@ Pass plan_pass(const fdtd_ctx* c, int mode, int T, int cus)
 struct SweepState {
     int cus = 0;
     int mode = -1;
-    Pass pass[kMaxT + 1];  // the plan of a pass of T steps, for `mode`
+    Pass pass[kMaxT + 1];    // the plan of a pass of T steps, for `mode`
+    int hooked_mode = -1;
+    Pass forward[kMaxT + 1], reverse[kMaxT + 1];  // of the adjoint's passes
     unsigned* pace = nullptr;
     int pace_words = 0;  // of one of the two alternating halves
     int turn = 0;
@@ -496,7 +700,7 @@ bool capturing(const fdtd_ctx* ctx)
     return st != hipStreamCaptureStatusNone;
 }
 
-int plan(fdtd_ctx* ctx)
+int state(fdtd_ctx* ctx)
 {
     if (!ctx->sweep) {
         ctx->sweep = new (std::nothrow) SweepState();
@@ -509,9 +713,17 @@ int plan(fdtd_ctx* ctx)
         if (e != hipSuccess) return hip_fail(ctx, e, "sweep: device attribute");
         S->cus = std::max(1, v);
     }
+    return FDTD_OK;
+}
+
+int plan(fdtd_ctx* ctx)
+{
+    int rc = state(ctx);
+    if (rc) return rc;
+    SweepState* S = ctx->sweep;
     const int mode = mode_of(ctx);
     if (S->mode != mode) {
-        for (int T = 1; T <= kMaxT; ++T) S->pass[T] = plan_pass(ctx, mode, T, S->cus);
+        for (int T = 1; T <= kMaxT; ++T) S->pass[T] = plan_pass(ctx, mode, kUpdate, T, S->cus);
         S->mode = mode;
     }
     // Blocks are kept in step where the state is past 1 GiB: 512^3, T = 5,
@@ -538,28 +750,56 @@ int plan(fdtd_ctx* ctx)
     return FDTD_OK;
 }
 
-// Steps of the passes that advance n steps: as few as the cheapest split
-// takes, lengths within one of each other, an even number of them when `even`.
-int split(const SweepState* S, int64_t n, bool even, int64_t* passes)
+// Number of passes that advance n steps (0: none fits): as few as the cheapest
+// split takes, lengths within one of each other, the longer ones first; an
+// even number when `even`.
+int64_t split(const Pass* pass, int64_t n, bool even)
 {
     double best = 1e300;
     int64_t bp = 0;
     for (int T = 1; T <= kMaxT; ++T) {
-        if (!S->pass[T].v) continue;
+        if (!pass[T].v) continue;
         int64_t p = (n + T - 1) / T;
         if (even && (p & 1)) ++p;
         if (p > n) continue;
         const int t = (int)(n / p);
         const int64_t longer = n % p;
-        if (t + (longer ? 1 : 0) > kMaxT || !S->pass[t].v || (longer && !S->pass[t + 1].v)) continue;
-        const double us = (double)(p - longer) * S->pass[t].us + (longer ? (double)longer * S->pass[t + 1].us : 0.0);
+        if (t + (longer ? 1 : 0) > kMaxT || !pass[t].v || (longer && !pass[t + 1].v)) continue;
+        const double us = (double)(p - longer) * pass[t].us + (longer ? (double)longer * pass[t + 1].us : 0.0);
         if (us < best) {
             best = us;
             bp = p;
         }
     }
-    *passes = bp;
-    return bp > 0;
+    return bp;
+}
+
+SweepArgs base_args(const fdtd_ctx* ctx)
+{
+    SweepArgs A{};
+    A.cH = ctx->cH;
+    A.nx = ctx->nx;
+    A.ny = ctx->ny;
+    A.nz = ctx->nz;
+    for (int c = 0; c < 3; ++c) {
+        A.cE[c] = ctx->coef[c];
+        A.ca[c] = ctx->ca[c];
+    }
+    return A;
+}
+
+unsigned blocks_of(const Pass& P) { return (unsigned)((P.ntiles + kXCD - 1) / kXCD * kXCD); }
+
+void launch_pass(const fdtd_ctx* ctx, const Pass& P, SweepArgs& A, const HookArgs* K = nullptr)
+{
+    A.gz = P.gz;
+    A.gy = P.gy;
+    A.xchunk = P.xchunk;
+    A.ntiles = (int)P.ntiles;
+    if (K)
+        hipLaunchKernelGGL(P.v->hooked, dim3(blocks_of(P)), dim3(64 * P.v->W), 0, ctx->stream, A, *K);
+    else
+        hipLaunchKernelGGL(P.v->kern, dim3(blocks_of(P)), dim3(64 * P.v->W), 0, ctx->stream, A);
 }
 
 }  // namespace
@@ -613,17 +853,9 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
     int rc = sweep_prepare(ctx);
     if (rc) return rc;
     SweepState* S = ctx->sweep;
-    int64_t passes = 0;
-    if (!split(S, n, even && n > 1, &passes)) return fail(ctx, FDTD_EUNSUPPORTED, "sweep: no pass fits this call");
-    SweepArgs A;
-    A.cH = ctx->cH;
-    A.nx = ctx->nx;
-    A.ny = ctx->ny;
-    A.nz = ctx->nz;
-    for (int c = 0; c < 3; ++c) {
-        A.cE[c] = ctx->coef[c];
-        A.ca[c] = ctx->ca[c];
-    }
+    const int64_t passes = split(S->pass, n, even && n > 1);
+    if (passes == 0) return fail(ctx, FDTD_EUNSUPPORTED, "sweep: no pass fits this call");
+    SweepArgs A = base_args(ctx);
     A.id = ctx->mat_id8;
     A.tab = ctx->mat_tab8;
     A.ntab = ctx->ntab8;
@@ -635,15 +867,11 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
         const Pass& P = S->pass[t0 + (longer ? 1 : 0)];
         S->steps = t0 + (longer ? 1 : 0);
         S->tiles = (int)P.ntiles;
-        S->blocks = (int)((P.ntiles + kXCD - 1) / kXCD * kXCD);
+        S->blocks = (int)blocks_of(P);
     }
     for (int64_t p = 0; p < passes; ++p) {
         const int T = t0 + (p < longer ? 1 : 0);
         const Pass& P = S->pass[T];
-        A.gz = P.gz;
-        A.gy = P.gy;
-        A.xchunk = P.xchunk;
-        A.ntiles = (int)P.ntiles;
         for (int c = 0; c < 6; ++c) {
             A.in[c] = ctx->field[c];
             A.out[c] = ctx->alt[c];
@@ -653,15 +881,111 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
         A.pace_next = S->pace ? S->pace + (size_t)(S->turn ^ 1) * S->pace_words : nullptr;
         A.pace_words = S->pace_words;
         S->turn ^= 1;
-        const unsigned blocks = (unsigned)((P.ntiles + kXCD - 1) / kXCD * kXCD);
         PendingTiming t;
         timing_begin(ctx, kernel, &t);
-        hipLaunchKernelGGL(P.v->kern, dim3(blocks), dim3(64 * P.v->W), 0, ctx->stream, A);
+        launch_pass(ctx, P, A);
         timing_end(ctx, &t);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(ctx, e, "launch(sweep)");
         for (int c = 0; c < 6; ++c) std::swap(ctx->field[c], ctx->alt[c]);
         ctx->step_count += T;
+    }
+    return FDTD_OK;
+}
+
+bool sweep_hooked_ready(fdtd_ctx* ctx)
+{
+    if (!sweep_ready(ctx) || state(ctx) != FDTD_OK) return false;
+    SweepState* S = ctx->sweep;
+    const int mode = ctx->ca[0] ? kLossy : kArrays;
+    if (S->hooked_mode != mode) {
+        for (int T = 1; T <= kMaxT; ++T) {
+            S->forward[T] = plan_pass(ctx, mode, kForward, T, S->cus);
+            S->reverse[T] = plan_pass(ctx, mode, kReverse, T, S->cus);
+        }
+        S->hooked_mode = mode;
+    }
+    return true;
+}
+
+namespace {
+
+HookArgs hook_args(const SweepHooks& h)
+{
+    HookArgs K{};
+    for (int a = 0; a < 3; ++a) {
+        K.dlo[a] = h.des_lo[a];
+        K.dn[a] = h.des_n[a];
+        K.mlo[a] = h.mon_lo[a];
+        K.mn[a] = h.mon_n[a];
+    }
+    K.comp = h.comp;
+    K.F = h.F;
+    return K;
+}
+
+void hook_phase(HookArgs* K, const SweepHooks& h, int l, int64_t n)
+{
+    const double th = h.omega * (double)n * h.dt;
+    K->cr[l] = cos(th);
+    K->ci[l] = -sin(th);
+}
+
+}  // namespace
+
+int sweep_forward(fdtd_ctx* ctx, const SweepHooks& h, int64_t n0, int64_t n, bool record, int64_t first)
+{
+    if (n == 0) return FDTD_OK;
+    SweepState* S = ctx->sweep;
+    const int64_t passes = split(S->forward, n, false);
+    if (passes == 0) return fail(ctx, FDTD_EUNSUPPORTED, "adjoint: no pass fits this run");
+    SweepArgs A = base_args(ctx);
+    A.src = ctx->dev_sources;
+    A.nsrc = ctx->dev_sources_n;
+    HookArgs K = hook_args(h);
+    K.stride = (ctx->ca[0] ? 6 : 3) * (long long)h.des_n[0] * h.des_n[1] * h.des_n[2];
+    int64_t done = 0;
+    for (int64_t p = 0; p < passes; ++p) {
+        const int T = (int)(n / passes) + (p < n % passes ? 1 : 0);
+        for (int l = 0; l < T; ++l) hook_phase(&K, h, l, n0 + done + l + 1);
+        K.hist = record ? h.hist + (first + done) * K.stride : nullptr;
+        for (int c = 0; c < 6; ++c) {
+            A.in[c] = ctx->field[c];
+            A.out[c] = ctx->alt[c];
+        }
+        A.step = ctx->step_count;
+        launch_pass(ctx, S->forward[T], A, &K);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(ctx, e, "launch(adjoint forward sweep)");
+        for (int c = 0; c < 6; ++c) std::swap(ctx->field[c], ctx->alt[c]);
+        ctx->step_count += T;
+        done += T;
+    }
+    return FDTD_OK;
+}
+
+int sweep_reverse(fdtd_ctx* ctx, const SweepHooks& h, float* lam[6], float* lam2[6], int64_t n0, int64_t n)
+{
+    SweepState* S = ctx->sweep;
+    const int64_t passes = split(S->reverse, n, false);
+    if (passes == 0) return fail(ctx, FDTD_EUNSUPPORTED, "adjoint: no pass fits this run");
+    SweepArgs A = base_args(ctx);
+    HookArgs K = hook_args(h);
+    K.stride = 3 * (long long)h.des_n[0] * h.des_n[1] * h.des_n[2];
+    int64_t left = n;
+    for (int64_t p = 0; p < passes; ++p) {
+        const int T = (int)(n / passes) + (p < n % passes ? 1 : 0);
+        for (int l = 0; l < T; ++l) hook_phase(&K, h, l, n0 + left - l);
+        K.hist = h.back + (n - left) * K.stride;
+        for (int c = 0; c < 6; ++c) {
+            A.in[c] = lam[c];
+            A.out[c] = lam2[c];
+        }
+        launch_pass(ctx, S->reverse[T], A, &K);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(ctx, e, "launch(adjoint reverse sweep)");
+        for (int c = 0; c < 6; ++c) std::swap(lam[c], lam2[c]);
+        left -= T;
     }
     return FDTD_OK;
 }
