@@ -228,7 +228,8 @@ int fdtd_prepare(fdtd_ctx* ctx, int64_t nsteps);
  * over a shared queue of subdomain tickets (the paper's tile traversal of
  * Section 3 extended over several simulations).  The result of each context
  * is bit-identical to fdtd_step on it alone; the systolic scheme is used
- * whatever each context's scheme option.  The launch runs on ctxs[0]'s
+ * whatever each context's scheme option (and where every member would sweep,
+ * the batch does, in one launch per pass).  The launch runs on ctxs[0]'s
  * stream, after the work already queued on every member's stream, and every
  * member's stream continues after it.  Launch options (band steps, grid,
  * spin limit) are ctxs[0]'s; a wait timeout is reported by every member.

@@ -488,6 +488,7 @@ int fdtd_destroy(fdtd_ctx* ctx)
     release_material_ids(ctx);
     release_step_graph(ctx);
     sweep_release(ctx);
+    sweep_batch_release(ctx);
     for (int c = 0; c < 6; ++c) {
         if (ctx->field[c]) (void)hipFree(ctx->field[c]);
         if (ctx->field16[c]) (void)hipFree(ctx->field16[c]);

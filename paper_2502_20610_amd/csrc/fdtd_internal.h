@@ -39,6 +39,7 @@ struct PendingTiming {
 struct SystolicState;  // defined in systolic.hip
 struct StepGraph;      // defined in plain.hip
 struct SweepState;     // defined in sweep.hip
+struct SweepBatch;     // defined in sweep_batch.hip
 
 }  // namespace fdtd
 
@@ -100,6 +101,7 @@ struct fdtd_ctx {
     float* mat_tab8;
     int ntab8;
     fdtd::SweepState* sweep;
+    fdtd::SweepBatch* sweep_batch;  // of the batches this context leads
     int tile_wx;      // FDTD_OPT_TILE_X: 0 (the launch's default), 11, 15 or 19
     int auto_wx;      // the default width of the last systolic launch (19 or 15; 0 before)
     bool tune_plain;  // FDTD_OPT_AUTOTUNE_PLAIN
@@ -150,6 +152,11 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);
 // The longest pass, the blocks and the tiles of the last sweep of the context.
 void sweep_shape(const fdtd_ctx* ctx, int* steps, int* blocks, int* tiles);
 void sweep_release(fdtd_ctx* ctx);
+// Advance the contexts by nsteps >= 2 each, one launch per pass for all, on
+// cs[0]'s stream; every member has its second field set, and all are
+// conductive or none.  *done: false when no split of nsteps fits.
+int sweep_batch_steps(fdtd_ctx* const* cs, int n, int64_t nsteps, bool* done);
+void sweep_batch_release(fdtd_ctx* ctx);
 
 // What the adjoint of a monitor objective adds to a sweep (adjoint.hip): the
 // monitor transform F and the design-box history of the forward run, the

@@ -1923,7 +1923,32 @@ int systolic_step(fdtd_ctx* ctx, int64_t nsteps)
     return launch(one, 1, nsteps);
 }
 
-int systolic_step_batch(fdtd_ctx* const* ctxs, int n, int64_t nsteps) { return launch(ctxs, n, nsteps); }
+// A batch sweeps when each of its members would by itself (the lead's options
+// are the launch's, so the members' own leave it to the persistent launch too)
+// and they could share one launch.  64 steps of 16 grids of 16 to 64 cells an
+// axis: 1840 us as one persistent launch, 810 us as sweeps (read-outs included).
+int systolic_step_batch(fdtd_ctx* const* ctxs, int n, int64_t nsteps)
+{
+    // (what the persistent launch refuses stays refused: it compares the tile
+    // widths of the members' last launches)
+    bool sweeps = true;
+    std::vector<int> auto_wx(n);
+    for (int i = 0; i < n; ++i) {
+        auto_wx[i] = ctxs[i]->auto_wx;
+        sweeps = sweeps && (ctxs[i]->ca[0] != nullptr) == (ctxs[0]->ca[0] != nullptr) && tile_x(ctxs[i]) == tile_x(ctxs[0]);
+    }
+    for (int i = 0; i < n && sweeps; ++i) sweeps = sweeps_instead(ctxs[i], nsteps);
+    for (int i = 0; i < n && sweeps; ++i) sweeps = sweep_prepare(ctxs[i]) == FDTD_OK;
+    if (sweeps) {
+        bool done = false;
+        const int rc = sweep_batch_steps(ctxs, n, nsteps, &done);
+        const int wx = wide_tile_ok(ctxs, n) ? WX_WIDE : WX;
+        for (int i = 0; i < n; ++i) ctxs[i]->auto_wx = wx;
+        if (rc || done) return rc;
+    }
+    for (int i = 0; i < n; ++i) ctxs[i]->auto_wx = auto_wx[i];
+    return launch(ctxs, n, nsteps);
+}
 
 int systolic_prepare(fdtd_ctx* ctx, int64_t nsteps)
 {

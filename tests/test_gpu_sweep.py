@@ -83,3 +83,39 @@ def test_sweep_many_sources():
             sim.close()
         ref = oracle.run(zero, [eps] * 3, bc, 0.5, 1.0, 13, sources=sources, dtype=np.float32)
         assert_bitwise(got, ref, "%d sources" % count)
+
+
+@pytest.mark.parametrize("kinds", [("table",) * 4, ("table", "arrays") * 2, ("lossy table",) * 4,
+                                   ("lossy arrays", "lossy table") * 2])
+def test_sweep_batch_bitwise(kinds):
+    """Members of different sizes, boundaries and streams in one launch per
+    pass, over calls of several lengths; members at different step counts."""
+    shapes = [((16, 16, 16), (PEC, PEC, PEC)), ((23, 30, 57), (PER, PEC, PEC)), ((40, 17, 20), (PEC, PER, PER)),
+              ((9, 65, 33), (PEC, PEC, PEC))]
+    rng = np.random.default_rng(len(kinds[0]) + len(kinds[1]))
+    sims, work = [], []
+    try:
+        for q, ((shape, bc), kind) in enumerate(zip(shapes, kinds)):
+            eps, sigma = _materials(kind, shape, rng)
+            fields = wl.zero_pec([rng.uniform(-1, 1, shape).astype(np.float32) for _ in range(6)], bc)
+            src = wl.dipole(2, *(n // 2 for n in shape), rng.uniform(-1, 1, 30).astype(np.float32), first_step=q)
+            sim = fdtd.Simulation(shape, 0.5, 1.0, bc, scheme="systolic")
+            sims.append(sim)
+            sim.set_materials(eps, sigma=sigma)
+            sim.set_fields(fields)
+            sim.add_source(src["comp"], src["i"], src["j"], src["k"], src["waveform"], src["first_step"])
+            work.append((shape, bc, eps, sigma, fields, src))
+        sims[1].set_option(fdtd.OPT_SCHEME, fdtd.SCHEME_PLAIN)
+        sims[1].step(3)
+        done = [0, 3, 0, 0]
+        for n in (2, 7, 4, 13):
+            fdtd.step_batch(sims, n)
+            done = [d + n for d in done]
+        for sim, d, (shape, bc, eps, sigma, fields, src) in zip(sims, done, work):
+            assert sim.current_step == d
+            ref = oracle.run(fields, [eps] * 3, bc, 0.5, 1.0, d, sources=[src], dtype=np.float32,
+                             sigma=None if sigma is None else [sigma] * 3)
+            assert_bitwise(sim.read_fields(), ref, "batch member %s %s" % (shape, kinds))
+    finally:
+        for sim in sims:
+            sim.close()
