@@ -4,6 +4,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <string>
 
@@ -72,6 +73,32 @@ __global__ void from_f16_kernel(const uint16_t* __restrict__ src, float* __restr
     for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < n;
          p += (long long)gridDim.x * blockDim.x)
         dst[p] = from_h(src[p]) * scale;
+}
+
+// Read-out to device arrays, all components in one launch (blockIdx.y picks
+// one): a copy each costs a launch of 2-3 us, which on small grids is the
+// longer part (96 of them a third of a batch of 16 grids).  V: 16-byte moves
+// where every array is aligned to them, else words.
+struct Arrays6 {
+    const float* src[6];
+    float* dst[6];
+};
+
+template <typename V>
+__global__ __launch_bounds__(kThreads) void copy_fields_kernel(Arrays6 A, long long n)
+{
+    const V* const src = (const V*)A.src[blockIdx.y];
+    V* const dst = (V*)A.dst[blockIdx.y];
+    const long long stride = (long long)gridDim.x * kThreads;
+    long long p = (long long)blockIdx.x * kThreads + threadIdx.x;
+    for (; p + 3 * stride < n; p += 4 * stride) {
+        const V a = src[p], b = src[p + stride], c = src[p + 2 * stride], d = src[p + 3 * stride];
+        dst[p] = a;
+        dst[p + stride] = b;
+        dst[p + 2 * stride] = c;
+        dst[p + 3 * stride] = d;
+    }
+    for (; p < n; p += stride) dst[p] = src[p];
 }
 
 // Re-encode binary16 values under a new scale: h * old * inv_new.
@@ -280,6 +307,16 @@ int hip_fail(fdtd_ctx* ctx, hipError_t e, const char* what)
     std::string msg = std::string(what) + ": " + hipGetErrorString(e);
     if (ctx) ctx->poisoned = true;
     return fail(ctx, FDTD_EHIP, msg);
+}
+
+bool stream_capturing(const fdtd_ctx* ctx)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
 }
 
 void timing_begin(fdtd_ctx* ctx, int kernel, PendingTiming* t)
@@ -807,6 +844,37 @@ int fdtd_read_fields(fdtd_ctx* ctx, uint32_t comp_mask, float* const dst[6], int
     if (h16 && where == FDTD_HOST && comp_mask && (e = hipMalloc(&stage, bytes)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, FDTD_ENOMEM, "read_fields: staging allocation failed");
+    }
+    // one launch for arrays on this device; copies, which take or refuse any
+    // pointer, for others (and in a captured stream)
+    bool here = !h16 && where == FDTD_DEVICE && comp_mask && !stream_capturing(ctx);
+    for (int c = 0; c < 6 && here; ++c) {
+        hipPointerAttribute_t at;
+        if (!(comp_mask >> c & 1u)) continue;
+        here = hipPointerGetAttributes(&at, dst[c]) == hipSuccess && at.type == hipMemoryTypeDevice &&
+               at.device == ctx->device;
+        if (!here) (void)hipGetLastError();
+    }
+    if (here) {
+        Arrays6 A{};
+        unsigned m = 0;
+        uintptr_t bits = (uintptr_t)ctx->ncell * sizeof(float);  // a whole number of 16-byte moves?
+        for (int c = 0; c < 6; ++c) {
+            if (!(comp_mask >> c & 1u)) continue;
+            A.src[m] = ctx->field[c];
+            A.dst[m++] = dst[c];
+            bits |= (uintptr_t)ctx->field[c] | (uintptr_t)dst[c];
+        }
+        const bool wide = bits % sizeof(float4) == 0;
+        const long long n = wide ? ctx->ncell / 4 : ctx->ncell;
+        const dim3 grid((unsigned)std::max<long long>(1, std::min<long long>((n + 4 * kThreads - 1) / (4 * kThreads), 2048)), m);
+        if (wide)
+            hipLaunchKernelGGL(copy_fields_kernel<float4>, grid, dim3(kThreads), 0, ctx->stream, A, n);
+        else
+            hipLaunchKernelGGL(copy_fields_kernel<float>, grid, dim3(kThreads), 0, ctx->stream, A, n);
+        e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(ctx, e, "read_fields");
+        return FDTD_OK;
     }
     for (int c = 0; c < 6 && e == hipSuccess; ++c) {
         if (!(comp_mask >> c & 1u)) continue;

@@ -126,6 +126,9 @@ constexpr int64_t kDefaultSpinLimit = int64_t(1) << 22;
 int fail(fdtd_ctx* ctx, int code, const std::string& msg);
 int hip_fail(fdtd_ctx* ctx, hipError_t e, const char* what);
 
+// Whether the context's stream is being captured into a graph.
+bool stream_capturing(const fdtd_ctx* ctx);
+
 // Timing wrappers around a launch on ctx->stream (no-ops when profiling is off).
 void timing_begin(fdtd_ctx* ctx, int kernel, PendingTiming* t);
 void timing_end(fdtd_ctx* ctx, PendingTiming* t);

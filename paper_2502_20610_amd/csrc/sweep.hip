@@ -134,16 +134,6 @@ __global__ void clear_words(unsigned* p, int n)
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) p[q] = 0u;
 }
 
-bool capturing(const fdtd_ctx* ctx)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 int state(fdtd_ctx* ctx)
 {
     if (!ctx->sweep) {
@@ -173,7 +163,7 @@ int plan(fdtd_ctx* ctx)
     // Blocks are kept in step where the state is past 1 GiB: 512^3, T = 5,
     // 225 -> 256 G cell updates/s, 1024 x 1024 x 512 255 -> 269; at 256^3,
     // one round of blocks, 202 against 205.
-    if (!S->pace && 24.0 * (double)ctx->ncell > 1.0737e9 && !capturing(ctx)) {
+    if (!S->pace && 24.0 * (double)ctx->ncell > 1.0737e9 && !stream_capturing(ctx)) {
         long long words = 0;
         for (int T = 1; T <= kMaxT; ++T) {
             const Pass& p = S->pass[T];
@@ -262,7 +252,7 @@ bool sweep_ready(fdtd_ctx* ctx)
     if (have) return true;
     // a scheme that can do without the second field set takes it only where
     // three quarters of the free memory stay free
-    if (capturing(ctx)) return false;
+    if (stream_capturing(ctx)) return false;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
         (void)hipGetLastError();

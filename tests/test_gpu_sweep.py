@@ -119,3 +119,32 @@ def test_sweep_batch_bitwise(kinds):
     finally:
         for sim in sims:
             sim.close()
+
+
+@pytest.mark.parametrize("shape", [(5, 7, 9), (16, 20, 24), (33, 64, 31)])
+def test_device_read_out(shape):
+    """Read-outs to device arrays: whole, by mask, and to arrays that are not
+    aligned for wide moves, against the host read-out."""
+    import torch
+    rng = np.random.default_rng(shape[0])
+    sim = fdtd.Simulation(shape, 0.5, 1.0, (PER, PER, PER), scheme="plain")
+    try:
+        sim.set_fields([rng.uniform(-1, 1, shape).astype(np.float32) for _ in range(6)])
+        want = sim.read_fields()
+        n = shape[0] * shape[1] * shape[2]
+        for shift in (0, 1):
+            for mask in (0x3F, 0x2A, 0x01):
+                buf = torch.full((6, n + 8), 7.0, device="cuda")
+                out = [buf[c, shift:shift + n].view(shape) for c in range(6)]
+                torch.cuda.synchronize()
+                sim.read_fields(mask=mask, out=out)
+                sim.synchronize()
+                got = buf.cpu().numpy()
+                for c in range(6):
+                    if mask >> c & 1:
+                        assert np.array_equal(got[c, shift:shift + n].view(np.uint32), want[c].ravel().view(np.uint32))
+                    else:
+                        assert np.all(got[c] == 7.0)
+                    assert np.all(got[c, :shift] == 7.0) and np.all(got[c, shift + n:] == 7.0)
+    finally:
+        sim.close()
