@@ -309,6 +309,24 @@ int hip_fail(fdtd_ctx* ctx, hipError_t e, const char* what)
     return fail(ctx, FDTD_EHIP, msg);
 }
 
+int widen_fields(fdtd_ctx* ctx, float* const dst[6])
+{
+    for (int c = 0; c < 6; ++c)
+        hipLaunchKernelGGL(from_f16_kernel, dim3(grid_for(ctx->ncell)), dim3(kThreads), 0, ctx->stream, ctx->field16[c],
+                           dst[c], (long long)ctx->ncell, ldexpf(1.0f, ctx->fexp[c]));
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? FDTD_OK : hip_fail(ctx, e, "launch(widen fields)");
+}
+
+int narrow_fields(fdtd_ctx* ctx, float* const src[6])
+{
+    for (int c = 0; c < 6; ++c)
+        hipLaunchKernelGGL(to_f16_kernel, dim3(grid_for(ctx->ncell)), dim3(kThreads), 0, ctx->stream, src[c],
+                           ctx->field16[c], (long long)ctx->ncell, ldexpf(1.0f, -ctx->fexp[c]));
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? FDTD_OK : hip_fail(ctx, e, "launch(narrow fields)");
+}
+
 bool stream_capturing(const fdtd_ctx* ctx)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -530,6 +548,7 @@ int fdtd_destroy(fdtd_ctx* ctx)
         if (ctx->field[c]) (void)hipFree(ctx->field[c]);
         if (ctx->field16[c]) (void)hipFree(ctx->field16[c]);
         if (ctx->alt[c]) (void)hipFree(ctx->alt[c]);
+        if (ctx->wide[c]) (void)hipFree(ctx->wide[c]);
     }
     for (int c = 0; c < 3; ++c) {
         if (ctx->coef[c]) (void)hipFree(ctx->coef[c]);

@@ -62,6 +62,7 @@ struct fdtd_ctx {
     int fexp[6];      // FP16 storage: power-of-two scale exponent per field component
     float* ca[3];     // E decay per step with conductivity; null when lossless
     float* alt[6];    // second field set of the sweeps (allocated on first use)
+    float* wide[6];   // FP16 storage: the first one, FP32 for the length of a call
     float cH;
 
     std::vector<fdtd::SourceRec> sources;
@@ -126,6 +127,11 @@ constexpr int64_t kDefaultSpinLimit = int64_t(1) << 22;
 int fail(fdtd_ctx* ctx, int code, const std::string& msg);
 int hip_fail(fdtd_ctx* ctx, hipError_t e, const char* what);
 
+// FP16 storage: the six fields to FP32 arrays (times their scales, exactly), and
+// back, rounded once.
+int widen_fields(fdtd_ctx* ctx, float* const dst[6]);
+int narrow_fields(fdtd_ctx* ctx, float* const src[6]);
+
 // Whether the context's stream is being captured into a graph.
 bool stream_capturing(const fdtd_ctx* ctx);
 
@@ -143,7 +149,7 @@ int plain_fused_step(fdtd_ctx* ctx, int64_t nsteps);
 int plain_fused_prepare(fdtd_ctx* ctx);
 
 // Sweep: several steps per pass into the second field set, whose pointers
-// trade places with ctx->field after every pass (sweep.hip).  FP32 storage.
+// trade places with ctx->field after every pass (sweep.hip).
 bool sweep_supported(const fdtd_ctx* ctx);
 // Whether a scheme that does not need the second field set should sweep: it
 // is there, or fits well (and is then allocated).
@@ -153,6 +159,10 @@ int sweep_prepare(fdtd_ctx* ctx);
 // steps or more ends in the arrays it started from.
 int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);
 // The longest pass, the blocks and the tiles of the last sweep of the context.
+// FP16 storage: advance n steps by sweeps over FP32 copies of the state,
+// rounded to binary16 after every `band` steps and at the end (both field sets
+// are allocated by sweep_ready).
+int sweep_half_steps(fdtd_ctx* ctx, int64_t n, int64_t band, int kernel);
 void sweep_shape(const fdtd_ctx* ctx, int* steps, int* blocks, int* tiles);
 void sweep_release(fdtd_ctx* ctx);
 // Advance the contexts by nsteps >= 2 each, one launch per pass for all, on

@@ -258,8 +258,7 @@ int build_material_ids(fdtd_ctx* ctx)
     if (!lossy && (!ensure(&ctx->mat_id, nc) || !ensure(&ctx->mat_tab, (size_t)kMaxMaterials * 3)))
         return FDTD_OK;  // no room: the per-cell arrays serve
     // (a change between lossless and conductive goes through release_material_ids)
-    const bool bytes = ctx->storage == FDTD_FP32 && ensure(&ctx->mat_id8, nc) &&
-                       ensure(&ctx->mat_tab8, (size_t)kMaxMaterials * 6);
+    const bool bytes = ensure(&ctx->mat_id8, nc) && ensure(&ctx->mat_tab8, (size_t)kMaxMaterials * 6);
     if (lossy && !bytes) return FDTD_OK;
     std::vector<unsigned> tab;
     int count = 0;

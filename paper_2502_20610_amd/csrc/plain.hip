@@ -366,7 +366,7 @@ int plain_step(fdtd_ctx* ctx, int64_t nsteps)
 // 3.3 against 5.9 and 8.1 against 14.8).  A single step stays in place.
 bool plain_sweeps(const fdtd_ctx* ctx, int64_t nsteps)
 {
-    return nsteps > 1 && !ctx->profile && sweep_supported(ctx);
+    return nsteps > 1 && !ctx->profile && ctx->storage == FDTD_FP32 && sweep_supported(ctx);
 }
 
 int plain_fused_prepare(fdtd_ctx* ctx)

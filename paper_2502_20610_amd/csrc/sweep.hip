@@ -241,14 +241,16 @@ SweepArgs sweep::base_args(const fdtd_ctx* ctx)
 // A plane must fit a buffer descriptor with room for the dropped offset.
 bool sweep_supported(const fdtd_ctx* ctx)
 {
-    return ctx->storage == FDTD_FP32 && (uint64_t)ctx->ny * (uint64_t)ctx->nz * 4u < (uint64_t)kDropped;
+    // (FP16 storage: with the coefficients' exact values in a table)
+    return (ctx->storage == FDTD_FP32 || mode_of(ctx) == kTable) && (uint64_t)ctx->ny * (uint64_t)ctx->nz * 4u < (uint64_t)kDropped;
 }
 
 bool sweep_ready(fdtd_ctx* ctx)
 {
     if (!sweep_supported(ctx)) return false;
+    const bool half = ctx->storage == FDTD_FP16_STORAGE;
     bool have = true;
-    for (int c = 0; c < 6; ++c) have = have && ctx->alt[c];
+    for (int c = 0; c < 6; ++c) have = have && ctx->alt[c] && (!half || ctx->wide[c]);
     if (have) return true;
     // a scheme that can do without the second field set takes it only where
     // three quarters of the free memory stay free
@@ -258,11 +260,12 @@ bool sweep_ready(fdtd_ctx* ctx)
         (void)hipGetLastError();
         return false;
     }
-    if (24.0 * (double)ctx->ncell > 0.25 * (double)free_b) return false;
+    if ((half ? 48.0 : 24.0) * (double)ctx->ncell > 0.25 * (double)free_b) return false;
     if (sweep_prepare(ctx) == FDTD_OK) return true;
     for (int c = 0; c < 6; ++c) {
         if (ctx->alt[c]) (void)hipFree(ctx->alt[c]);
-        ctx->alt[c] = nullptr;
+        if (ctx->wide[c]) (void)hipFree(ctx->wide[c]);
+        ctx->alt[c] = ctx->wide[c] = nullptr;
     }
     return false;
 }
@@ -271,21 +274,24 @@ int sweep_prepare(fdtd_ctx* ctx)
 {
     const size_t bytes = (size_t)ctx->ncell * sizeof(float);
     for (int c = 0; c < 6; ++c)
-        if (!ctx->alt[c]) {
-            hipError_t e = hipMalloc(&ctx->alt[c], bytes);
+        for (float** p : {&ctx->alt[c], &ctx->wide[c]}) {
+            if (*p || (p == &ctx->wide[c] && ctx->storage == FDTD_FP32)) continue;
+            hipError_t e = hipMalloc(p, bytes);
             if (e != hipSuccess) {
                 (void)hipGetLastError();
-                ctx->alt[c] = nullptr;
+                *p = nullptr;
                 return fail(ctx, FDTD_ENOMEM, "fused plain step: second field set does not fit");
             }
         }
     return plan(ctx);
 }
 
-int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
+namespace {
+
+// n steps from `now` into `other` and back; the pointers trade places with
+// every pass, so `now` holds the state in the end.
+int run(fdtd_ctx* ctx, float* now[6], float* other[6], int64_t n, int kernel, bool even)
 {
-    int rc = sweep_prepare(ctx);
-    if (rc) return rc;
     SweepState* S = ctx->sweep;
     const int64_t passes = split(S->pass, n, even && n > 1);
     if (passes == 0) return fail(ctx, FDTD_EUNSUPPORTED, "sweep: no pass fits this call");
@@ -307,8 +313,8 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
         const int T = t0 + (p < longer ? 1 : 0);
         const Pass& P = S->pass[T];
         for (int c = 0; c < 6; ++c) {
-            A.in[c] = ctx->field[c];
-            A.out[c] = ctx->alt[c];
+            A.in[c] = now[c];
+            A.out[c] = other[c];
         }
         A.step = ctx->step_count;
         A.pace = S->pace ? S->pace + (size_t)S->turn * S->pace_words : nullptr;
@@ -321,8 +327,32 @@ int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
         timing_end(ctx, &t);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(ctx, e, "launch(sweep)");
-        for (int c = 0; c < 6; ++c) std::swap(ctx->field[c], ctx->alt[c]);
+        for (int c = 0; c < 6; ++c) std::swap(now[c], other[c]);
         ctx->step_count += T;
+    }
+    return FDTD_OK;
+}
+
+}  // namespace
+
+int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
+{
+    int rc = sweep_prepare(ctx);
+    if (rc) return rc;
+    return run(ctx, ctx->field, ctx->alt, n, kernel, even);
+}
+
+// The binary16 arrays are read and written once per band, as the persistent
+// launch does; the conversions move 72 B per cell and band.
+int sweep_half_steps(fdtd_ctx* ctx, int64_t n, int64_t band, int kernel)
+{
+    int rc = sweep_prepare(ctx);
+    if (rc) return rc;
+    for (int64_t done = 0; done < n; done += band) {
+        const int64_t k = std::min(band, n - done);
+        if ((rc = widen_fields(ctx, ctx->wide)) || (rc = run(ctx, ctx->wide, ctx->alt, k, kernel, false)) ||
+            (rc = narrow_fields(ctx, ctx->wide)))
+            return rc;
     }
     return FDTD_OK;
 }

@@ -1575,7 +1575,9 @@ bool wide_tile_ok(fdtd_ctx* const* cs, int n)
 // with periodic x and y 94 / 209, 256^3 conductive 109 / 195, 1024 x 1024 x
 // 512 in 20-step calls 163 / 255.  The persistent launch keeps:
 //   * calls with a systolic option of their own, which ask for that kernel;
-//   * FP16 storage, which rounds once per band;
+//   * FP16 storage with more than 256 materials (with a table, the bands are
+//     swept over FP32 copies of the state and rounded where they end: the same
+//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 19.3 ms);
 //   * single steps (a sweep would leave the state in the other arrays);
 //   * on all-PEC grids, calls of two 64-step bands or more (512^3 and up by
 //     the band model), whose band and ring slots FDTD_INFO_* reports
@@ -1913,9 +1915,13 @@ int systolic_supported(const fdtd_ctx* ctx, std::string* why)
 int systolic_step(fdtd_ctx* ctx, int64_t nsteps)
 {
     if (sweeps_instead(ctx, nsteps)) {
-        const int rc = sweep_steps(ctx, nsteps, FDTD_KERNEL_SYSTOLIC, true);
+        const bool half = ctx->storage == FDTD_FP16_STORAGE;
+        const int band = half ? default_band(&ctx, 1, nsteps) : 0;
+        const int rc = half ? sweep_half_steps(ctx, nsteps, band, FDTD_KERNEL_SYSTOLIC)
+                            : sweep_steps(ctx, nsteps, FDTD_KERNEL_SYSTOLIC, true);
         if (rc) return rc;
         sweep_shape(ctx, &ctx->sys_band, &ctx->sys_grid, &ctx->sys_tickets);
+        if (half) ctx->sys_band = band;  // (the steps between two roundings)
         ctx->sys_ring_slots = 0;
         return FDTD_OK;
     }
@@ -1935,7 +1941,7 @@ int systolic_step_batch(fdtd_ctx* const* ctxs, int n, int64_t nsteps)
     std::vector<int> auto_wx(n);
     for (int i = 0; i < n; ++i) {
         auto_wx[i] = ctxs[i]->auto_wx;
-        sweeps = sweeps && (ctxs[i]->ca[0] != nullptr) == (ctxs[0]->ca[0] != nullptr) && tile_x(ctxs[i]) == tile_x(ctxs[0]);
+        sweeps = sweeps && ctxs[i]->storage == FDTD_FP32 && (ctxs[i]->ca[0] != nullptr) == (ctxs[0]->ca[0] != nullptr) && tile_x(ctxs[i]) == tile_x(ctxs[0]);
     }
     for (int i = 0; i < n && sweeps; ++i) sweeps = sweeps_instead(ctxs[i], nsteps);
     for (int i = 0; i < n && sweeps; ++i) sweeps = sweep_prepare(ctxs[i]) == FDTD_OK;

@@ -148,3 +148,31 @@ def test_device_read_out(shape):
                     assert np.all(got[c, :shift] == 7.0) and np.all(got[c, shift + n:] == 7.0)
     finally:
         sim.close()
+
+
+@pytest.mark.parametrize("shape,bc,exp2", [((33, 20, 30), (PEC, PEC, PEC), (0,) * 6),
+                                           ((20, 40, 57), (PER, PEC, PER), (1, -2, 0, 3, -1, 2))])
+def test_half_storage_bands(shape, bc, exp2):
+    """FP16 storage over calls of several bands, one and less: rounded once per
+    band, as the FP16-storage oracle."""
+    from oracle import f16
+    w = wl.small_case(shape, bc, seed=sum(shape), nsteps=130, dipoles=[tuple(n // 2 for n in shape)])
+    sim = fdtd.Simulation(shape, w.dt, w.dx, bc, scheme="systolic", storage="fp16")
+    calls, bands = [], []
+    try:
+        sim.set_field_scale(exp2)
+        sim.set_materials(w.eps)
+        sim.set_fields(w.fields)
+        for s in w.sources:
+            sim.add_source(s["comp"], s["i"], s["j"], s["k"], s["waveform"])
+        for n in (70, 2, 1, 50):
+            sim.step(n)
+            calls.append(n)
+            bands.append(sim.info(fdtd.INFO_SYSTOLIC_BAND))
+        got = sim.read_fields()
+    finally:
+        sim.close()
+    assert bands[0] < calls[0]
+    ref = f16.run_systolic(w.fields, f16.coeff_E16(w.eps3(), bc, w.dt, w.dx), np.float32(w.dt / w.dx), calls, bands,
+                           sources=w.sources, exp2=exp2)
+    assert_bitwise(got, ref, "fp16 bands %s" % (shape,))
