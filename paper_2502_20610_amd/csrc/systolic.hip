@@ -1932,7 +1932,7 @@ int systolic_step(fdtd_ctx* ctx, int64_t nsteps)
 // A batch sweeps when each of its members would by itself (the lead's options
 // are the launch's, so the members' own leave it to the persistent launch too)
 // and they could share one launch.  64 steps of 16 grids of 16 to 64 cells an
-// axis: 1840 us as one persistent launch, 810 us as sweeps (read-outs included).
+// axis: 1840 us as one persistent launch, 690 us as sweeps (read-outs included).
 int systolic_step_batch(fdtd_ctx* const* ctxs, int n, int64_t nsteps)
 {
     // (what the persistent launch refuses stays refused: it compares the tile
