@@ -9,8 +9,8 @@ PEC box with 2000 random dielectric boxes and three dipoles, FP32.  Inputs
 are resident in HBM before the timed region; the timed region is K steps
 bracketed by stream synchronisation.  Prints ONE JSON line for the headline
 scheme (systolic when available, else plain), with the two plain schemes'
-figures alongside (one launch per half-step, and the fused one launch per
-step), a roofline object for the dominant kernel (per-launch
+figures alongside (timed kernel by kernel, which keeps them at one launch per
+half-step and one per step; untimed calls sweep several), a roofline object for the dominant kernel (per-launch
 device time from HIP events recorded on the library's stream inside the
 timed region) and the oracle timed on the host cores over a bounded sample.
 """
@@ -34,7 +34,7 @@ VALU_FP32_PEAK_TFLOPS = 256 * 64 * 2.4e9 / 1e12
 FLOPS_PER_CELL = 36            # 6 components x 6 flops (Section 2)
 PLAIN_E_BYTES, PLAIN_H_BYTES = 48, 36   # algorithmic bytes per cell, per half-step kernel
 PLAIN_BYTES_PER_UPDATE = PLAIN_E_BYTES + PLAIN_H_BYTES
-# fused plain step: E, H and cE in, E and H out
+# one launch per step: E, H and cE in, E and H out
 PLAIN_FUSED_BYTES_PER_UPDATE = 60
 
 
@@ -583,7 +583,7 @@ def main():
                   "steps": int(round(steps_per_launch)), "band": band, "materials": int(mats),
                   "tile_x": stats["info"]["tile"][0]}
         name = "sweep_kernel" if swept else "systolic_kernel"
-        traffic = counter_traffic(name, "paper_2502_20610_amd/csrc/%s.hip" % name[:-7],
+        traffic = counter_traffic(name, "paper_2502_20610_amd/csrc/" + ("sweep_tile.h" if swept else "systolic.hip"),
                                   dict(launch, cells=cells))
         # arithmetic intensity 36 / b_alg flop/B is below the machine balance
         # (39.3 T op/s / 8 TB/s), so the roofline bound is HBM

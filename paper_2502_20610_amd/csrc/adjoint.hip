@@ -33,6 +33,9 @@
 // the same history and runs its reverse steps.  When the whole history fits
 // in device memory, S = N: one segment, no checkpoint and no recompute.  The monitor
 // transform and the gradient accumulate in FP64; the adjoint fields are FP32.
+//
+// Both runs go as sweeps of up to five steps per pass (sweep_adjoint.hip); the
+// one-step kernels here run where the second sets of fields do not fit.
 #include "fdtd_internal.h"
 
 #include <math.h>

@@ -41,7 +41,6 @@ const Variant kVariants[] = {
 #undef V4
 #undef V5
 
-
 }  // namespace
 
 int sweep::mode_of(const fdtd_ctx* c)

@@ -1,4 +1,5 @@
-// Systolic scheme: one persistent launch per fdtd_step() call.
+// Systolic scheme: one persistent launch per fdtd_step() call, for the calls
+// that sweeps (sweep.hip) do not take over: see sweeps_instead().
 //
 // Method (paper, Sections 3 and 4): the grid is covered by subdomain tiles
 // that stay resident on chip for a band of K steps.  Every step a tile moves
@@ -1577,7 +1578,7 @@ bool wide_tile_ok(fdtd_ctx* const* cs, int n)
 //   * calls with a systolic option of their own, which ask for that kernel;
 //   * FP16 storage with more than 256 materials (with a table, the bands are
 //     swept over FP32 copies of the state and rounded where they end: the same
-//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 19.3 ms);
+//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 18.1 ms);
 //   * single steps (a sweep would leave the state in the other arrays);
 //   * on all-PEC grids, calls of two 64-step bands or more (512^3 and up by
 //     the band model), whose band and ring slots FDTD_INFO_* reports

@@ -427,8 +427,8 @@ def design_objective(eps_design, problem: DesignProblem):
 
 
 def step_batch(sims: Sequence["Simulation"], nsteps: int):
-    """Advance several Simulation objects by nsteps each in one persistent
-    systolic launch (fdtd_step_batch)."""
+    """Advance several Simulation objects by nsteps each, sharing every launch
+    (fdtd_step_batch)."""
     sims = list(sims)
     if not sims:
         raise ValueError("step_batch needs at least one simulation")
