@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfdtd.so")
 SOURCES = ["systolic.hip", "sweep.hip", "sweep_batch.hip", "sweep_adjoint.hip", "fdtd_api.hip", "plain.hip",
-           "adjoint.hip", "invariants.hip", "materials.hip", "autotune.hip", "plan.cpp"]
+           "adjoint.hip", "invariants.hip", "materials.hip", "autotune.hip", "plan.cpp", "sweep_plan.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",

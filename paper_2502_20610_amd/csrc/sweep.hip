@@ -1,5 +1,5 @@
-// Sweeps of one grid: kernels, the plan of a pass, launches (the tile itself is
-// in sweep_tile.h).
+// Sweeps of one grid: kernels and launches (the tile itself is in sweep_tile.h,
+// the plan of a pass in sweep_plan.cpp).
 #include <math.h>
 
 #include <algorithm>
@@ -19,27 +19,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
     if (!place(A, xcd, slot, per_xcd)) return;  // whole block
     sweep_tile<T, R, W, MODE, WHOLE, kUpdate>(A, HookArgs{}, S, xcd, slot, per_xcd);
 }
-#define V(T, R, W, M) {T, R, W, M, false, kUpdate, sweep_kernel<T, R, W, M, false>, nullptr}
-#define VW(T, W, M) {T, 1, W, M, true, kUpdate, sweep_kernel<T, 1, W, M, true>, nullptr}
-#define VW4(W, M) VW(1, W, M), VW(2, W, M), VW(3, W, M), VW(4, W, M)
-#define V2(R, W, M) V(1, R, W, M), V(2, R, W, M)
-#define V3(R, W, M) V2(R, W, M), V(3, R, W, M)
-#define V4(R, W, M) V3(R, W, M), V(4, R, W, M)
-#define V5(R, W, M) V4(R, W, M), V(5, R, W, M)
-const Variant kVariants[] = {
-    V5(3, 12, kTable),      V4(2, 16, kTable),     V4(1, 16, kTable),
-    V4(3, 12, kLossyTable), V5(2, 16, kLossyTable), V4(1, 16, kLossyTable),
-    V4(4, 8, kArrays),      V3(2, 16, kArrays), V4(1, 16, kArrays),
-    V3(3, 8, kLossy),       V2(2, 16, kLossy), V4(1, 16, kLossy),
-    VW4(16, kTable),        VW4(16, kArrays),    VW4(16, kLossyTable), VW4(16, kLossy),
-};
+#define V(T, R, W, M) sweep_kernel<T, R, W, M, false>,
+#define VW(T, W, M) sweep_kernel<T, 1, W, M, true>,
+void (*const kKernels[])(const SweepArgs) = {FDTD_SWEEP_SHAPES(V, VW)};
 #undef V
 #undef VW
-#undef VW4
-#undef V2
-#undef V3
-#undef V4
-#undef V5
 
 }  // namespace
 
@@ -49,69 +33,6 @@ int sweep::mode_of(const fdtd_ctx* c)
     return c->ca[0] ? (tab ? kLossyTable : kLossy) : (tab ? kTable : kArrays);
 }
 
-namespace {
-int in_bytes(int mode) { return 24 + (mode == kArrays ? 12 : mode == kLossy ? 24 : 1); }
-}  // namespace
-
-bool sweep::fits_cache(int mode, double cells) { return (24.0 + in_bytes(mode)) * cells <= 256e6; }
-
-double sweep::round_us(int mode, int rows, int T, int xc, bool cached)
-{
-    const double level = 0.11 + 0.29 * rows / 16.0;
-    const double bytes = rows * 64.0 * in_bytes(mode) + (rows - 2 * T) * (64 - 2 * T) * 24.0;
-    // (level l starts at iteration 2l)
-    const double compute = 0.45 * (xc + 2 * T) + level * (T * (T + 1) + (double)xc * T);
-    return std::max(compute, bytes / (cached ? 2.2 * 17600.0 : 17600.0) * (xc + 2 * T));
-}
-
-namespace {
-
-// The best pass of T steps by a model of a block's time, fitted to passes
-// measured from 32^3 to 1024 x 1024 x 512 (within 20%): 3 us for the launch;
-// per iteration 0.45 us and, for each level that runs, 0.11 us + 0.29 us per 16
-// rows; or the time the loads and stores of the iterations take at 17.6 KB/us
-// per CU (4.5 TB/s in all; 2.2 times that where everything sits in the
-// Infinity Cache), if that is longer; the last round of blocks counts in full.
-// Where a pass does not fill the device, fewer blocks leave room for another
-// context's (three contexts in turn, 48^3: chunks of one plane 3.3 us per step,
-// of two 2.1, and 4.4 for either alone): the blocks of a full device count 0.6 more.
-Pass plan_pass(const fdtd_ctx* c, int mode, int hook, int T, int cus)
-{
-    Pass best;
-    const bool cached = fits_cache(mode, (double)c->ncell);
-    int nv = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
-    const Variant* vs = hook == kUpdate ? kVariants : hooked_variants(&nv);
-    for (int i = 0; i < nv; ++i) {
-        const Variant& v = vs[i];
-        if (v.T != T || v.mode != mode || v.hook != hook || (v.whole && c->nz != 64)) continue;
-        const int rows = v.R * v.W, vz = v.whole ? 64 : 64 - 2 * T, vy = rows - 2 * T;
-        Pass p;
-        p.v = &v;
-        p.gz = (c->nz + vz - 1) / vz;
-        p.gy = (c->ny + vy - 1) / vy;
-        const long long base = (long long)p.gz * p.gy;
-        int last = 0;
-        for (int q = 1; q <= std::min(c->nx, 1024); ++q) {
-            const int xc = (c->nx + q - 1) / q;
-            if (xc == last) continue;
-            last = xc;
-            const long long nt = base * ((c->nx + xc - 1) / xc);
-            const double us = ((double)((nt + cus - 1) / cus) * round_us(mode, rows, T, xc, cached) + 3.0) *
-                              (1.0 + 0.6 * std::min(1.0, (double)nt / cus));
-            if (us < p.us) {
-                p.us = us;
-                p.xchunk = xc;
-                p.ntiles = nt;
-            }
-            if (nt > 64LL * cus) break;
-        }
-        if (p.us < best.us) best = p;
-    }
-    return best;
-}
-
-}  // namespace
-
 struct SweepState {
     int cus = 0;
     int mode = -1;
@@ -119,7 +40,7 @@ struct SweepState {
     int hooked_mode = -1;
     Pass forward[kMaxT + 1], reverse[kMaxT + 1];  // of the adjoint's passes
     unsigned* pace = nullptr;
-    int pace_words = 0;  // of one of the two alternating halves
+    int pace_words = 0;  // of one of the two alternating halves: enough for any mode
     int turn = 0;
     int steps = 0, blocks = 0, tiles = 0;  // of the last call's longest pass
 };
@@ -155,21 +76,17 @@ int plan(fdtd_ctx* ctx)
     if (rc) return rc;
     SweepState* S = ctx->sweep;
     const int mode = mode_of(ctx);
+    const int N[3] = {ctx->nx, ctx->ny, ctx->nz};
     if (S->mode != mode) {
-        for (int T = 1; T <= kMaxT; ++T) S->pass[T] = plan_pass(ctx, mode, kUpdate, T, S->cus);
+        for (int T = 1; T <= kMaxT; ++T) S->pass[T] = plan_pass(N, mode, kUpdate, T, S->cus);
         S->mode = mode;
     }
     // Blocks are kept in step where the state is past 1 GiB: 512^3, T = 5,
     // 225 -> 256 G cell updates/s, 1024 x 1024 x 512 255 -> 269; at 256^3,
-    // one round of blocks, 202 against 205.
+    // one round of blocks, 202 against 205.  The marks are allocated once, for
+    // whatever coefficients the context is given later.
     if (!S->pace && 24.0 * (double)ctx->ncell > 1.0737e9 && !stream_capturing(ctx)) {
-        long long words = 0;
-        for (int T = 1; T <= kMaxT; ++T) {
-            const Pass& p = S->pass[T];
-            if (!p.v) continue;
-            const long long groups = ((p.ntiles + kXCD - 1) / kXCD + kPaceGroup - 1) / kPaceGroup * kXCD;
-            words = std::max(words, groups * ((p.xchunk + 2 * T) / kPacePlanes + 1));
-        }
+        const long long words = most_mark_words(N, S->cus);
         if (words > 0 && words < (1 << 24)) {
             if (hipMalloc(&S->pace, 2 * (size_t)words * sizeof(unsigned)) != hipSuccess) {
                 (void)hipGetLastError();
@@ -191,13 +108,13 @@ int64_t split(const Pass* pass, int64_t n, bool even)
     double best = 1e300;
     int64_t bp = 0;
     for (int T = 1; T <= kMaxT; ++T) {
-        if (!pass[T].v) continue;
+        if (!pass[T].s) continue;
         int64_t p = (n + T - 1) / T;
         if (even && (p & 1)) ++p;
         if (p > n) continue;
         const int t = (int)(n / p);
         const int64_t longer = n % p;
-        if (t + (longer ? 1 : 0) > kMaxT || !pass[t].v || (longer && !pass[t + 1].v)) continue;
+        if (t + (longer ? 1 : 0) > kMaxT || !pass[t].s || (longer && !pass[t + 1].s)) continue;
         const double us = (double)(p - longer) * pass[t].us + (longer ? (double)longer * pass[t + 1].us : 0.0);
         if (us < best) {
             best = us;
@@ -216,9 +133,9 @@ void launch_pass(const fdtd_ctx* ctx, const Pass& P, SweepArgs& A, const HookArg
     A.xchunk = P.xchunk;
     A.ntiles = (int)P.ntiles;
     if (K)
-        hipLaunchKernelGGL(P.v->hooked, dim3(blocks_of(P)), dim3(64 * P.v->W), 0, ctx->stream, A, *K);
+        hipLaunchKernelGGL(hooked_kernel_of(P.index), dim3(blocks_of(P)), dim3(64 * P.s->W), 0, ctx->stream, A, *K);
     else
-        hipLaunchKernelGGL(P.v->kern, dim3(blocks_of(P)), dim3(64 * P.v->W), 0, ctx->stream, A);
+        hipLaunchKernelGGL(kKernels[P.index], dim3(blocks_of(P)), dim3(64 * P.s->W), 0, ctx->stream, A);
 }
 
 }  // namespace
@@ -316,10 +233,11 @@ int run(fdtd_ctx* ctx, float* now[6], float* other[6], int64_t n, int kernel, bo
             A.out[c] = other[c];
         }
         A.step = ctx->step_count;
-        A.pace = S->pace ? S->pace + (size_t)S->turn * S->pace_words : nullptr;
-        A.pace_next = S->pace ? S->pace + (size_t)(S->turn ^ 1) * S->pace_words : nullptr;
+        const bool paced = S->pace && mark_words(P) <= S->pace_words;
+        A.pace = paced ? S->pace + (size_t)S->turn * S->pace_words : nullptr;
+        A.pace_next = paced ? S->pace + (size_t)(S->turn ^ 1) * S->pace_words : nullptr;
         A.pace_words = S->pace_words;
-        S->turn ^= 1;
+        if (paced) S->turn ^= 1;
         PendingTiming t;
         timing_begin(ctx, kernel, &t);
         launch_pass(ctx, P, A);
@@ -362,9 +280,10 @@ bool sweep_hooked_ready(fdtd_ctx* ctx)
     SweepState* S = ctx->sweep;
     const int mode = ctx->ca[0] ? kLossy : kArrays;
     if (S->hooked_mode != mode) {
+        const int N[3] = {ctx->nx, ctx->ny, ctx->nz};
         for (int T = 1; T <= kMaxT; ++T) {
-            S->forward[T] = plan_pass(ctx, mode, kForward, T, S->cus);
-            S->reverse[T] = plan_pass(ctx, mode, kReverse, T, S->cus);
+            S->forward[T] = plan_pass(N, mode, kForward, T, S->cus);
+            S->reverse[T] = plan_pass(N, mode, kReverse, T, S->cus);
         }
         S->hooked_mode = mode;
     }

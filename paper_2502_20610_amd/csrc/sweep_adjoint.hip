@@ -28,21 +28,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
     else
         sweep_tile<T, R, W, MODE, false, HOOK == kReverse ? kTransposed : kUpdate>(A, K, S, xcd, slot, per_xcd);
 }
-#define VH(T, R, W, M) {T, R, W, M, false, kForward, nullptr, hooked_kernel<T, R, W, M, kForward>}, \
-    {T, R, W, M, false, kReverse, nullptr, hooked_kernel<T, R, W, M, kReverse>}
-const Variant kHooked[] = {
-    VH(1, 1, 16, kArrays), VH(2, 1, 16, kArrays), VH(3, 1, 16, kArrays), VH(4, 1, 16, kArrays),
-    VH(2, 4, 8, kArrays), VH(3, 4, 8, kArrays),
-    VH(1, 1, 16, kLossy), VH(2, 1, 16, kLossy), VH(3, 1, 16, kLossy), VH(2, 3, 8, kLossy), VH(3, 3, 8, kLossy),
-};
+#define VH(T, R, W, M) hooked_kernel<T, R, W, M, kForward>, hooked_kernel<T, R, W, M, kReverse>,
+const HookedKernel kKernels[] = {FDTD_SWEEP_HOOKED_SHAPES(VH)};
 #undef VH
 
 }  // namespace
 
-const Variant* sweep::hooked_variants(int* n)
-{
-    *n = (int)(sizeof(kHooked) / sizeof(kHooked[0]));
-    return kHooked;
-}
+HookedKernel sweep::hooked_kernel_of(int index) { return kKernels[index]; }
 
 }  // namespace fdtd

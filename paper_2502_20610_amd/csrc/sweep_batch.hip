@@ -39,13 +39,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
     sweep_tile<T, R, W, MODE, false, kUpdate>(A, HookArgs{}, S, 0, tile, A.ntiles);
 }
 
-struct Shape {
+struct BatchShape {
     int T, R, W, mode;
     void (*kern)(const SweepArgs*, const int2*, long long);
 };
 #define S(T, R, W, M) {T, R, W, M, batch_kernel<T, R, W, M>}
 #define S4(R, W, M) S(1, R, W, M), S(2, R, W, M), S(3, R, W, M), S(4, R, W, M)
-const Shape kShapes[] = {
+const BatchShape kShapes[] = {
     S4(1, 16, kTable), S4(2, 16, kTable), S4(1, 16, kArrays), S4(4, 8, kArrays),
     S4(1, 16, kLossyTable), S4(2, 16, kLossyTable), S4(1, 16, kLossy),
 };
@@ -56,7 +56,7 @@ constexpr int kMaxBatchT = 4;
 
 // One pass of T steps over every grid of the batch.
 struct BatchPass {
-    const Shape* s = nullptr;
+    const BatchShape* s = nullptr;
     int xcap = 0;  // planes of a chunk, at most
     double us = 1e300;
 };
@@ -67,7 +67,7 @@ int chunk(int nx, int cap)
     return (nx + q - 1) / q;
 }
 
-long long tiles(const fdtd_ctx* c, const Shape& s, int cap, int* gz, int* gy, int* xc)
+long long tiles(const fdtd_ctx* c, const BatchShape& s, int cap, int* gz, int* gy, int* xc)
 {
     const int vz = 64 - 2 * s.T, vy = s.R * s.W - 2 * s.T;
     *gz = (c->nz + vz - 1) / vz;
@@ -88,7 +88,7 @@ BatchPass plan(fdtd_ctx* const* cs, int n, int mode, int T, int cus)
     for (int i = 0; i < n; ++i) cells += (double)cs[i]->ncell;
     const bool cached = fits_cache(mode, cells);
     BatchPass best;
-    for (const Shape& s : kShapes) {
+    for (const BatchShape& s : kShapes) {
         if (s.T != T || s.mode != mode) continue;
         for (int cap = 1; cap <= 512; cap += std::max(1, cap / 4)) {
             long long nt = 0;
@@ -249,7 +249,7 @@ int sweep_batch_steps(fdtd_ctx* const* cs, int n, int64_t nsteps, bool* done)
     long long steps = 0;
     for (int64_t p = 0; p < passes; ++p) {
         const int k = p < longer ? 1 : 0;
-        const Shape& s = *pass[t + k].s;
+        const BatchShape& s = *pass[t + k].s;
         PendingTiming tm;
         timing_begin(lead, FDTD_KERNEL_SYSTOLIC, &tm);
         hipLaunchKernelGGL(s.kern, dim3((unsigned)nblocks[k]), dim3(64 * s.W), 0, st,

@@ -1,0 +1,96 @@
+// Host-side plan of a sweep (see sweep_plan.h).
+#include "sweep_plan.h"
+
+#include <algorithm>
+
+namespace fdtd {
+namespace sweep {
+
+namespace {
+
+#define V(T, R, W, M) {T, R, W, M, false, kUpdate},
+#define VW(T, W, M) {T, 1, W, M, true, kUpdate},
+#define VH(T, R, W, M) {T, R, W, M, false, kForward}, {T, R, W, M, false, kReverse},
+const Shape kShapes[] = {FDTD_SWEEP_SHAPES(V, VW)};
+const Shape kHookedShapes[] = {FDTD_SWEEP_HOOKED_SHAPES(VH)};
+#undef V
+#undef VW
+#undef VH
+
+int in_bytes(int mode) { return 24 + (mode == kArrays ? 12 : mode == kLossy ? 24 : 1); }
+
+}  // namespace
+
+bool fits_cache(int mode, double cells) { return (24.0 + in_bytes(mode)) * cells <= 256e6; }
+
+double round_us(int mode, int rows, int T, int xc, bool cached)
+{
+    const double level = 0.11 + 0.29 * rows / 16.0;
+    const double bytes = rows * 64.0 * in_bytes(mode) + (rows - 2 * T) * (64 - 2 * T) * 24.0;
+    // (level l starts at iteration 2l)
+    const double compute = 0.45 * (xc + 2 * T) + level * (T * (T + 1) + (double)xc * T);
+    return std::max(compute, bytes / (cached ? 2.2 * 17600.0 : 17600.0) * (xc + 2 * T));
+}
+
+// The model of a block's time, fitted to passes measured from 32^3 to 1024 x
+// 1024 x 512 (within 20%): 3 us for the launch; per iteration 0.45 us and, for
+// each level that runs, 0.11 us + 0.29 us per 16 rows; or the time the loads
+// and stores of the iterations take at 17.6 KB/us per CU (4.5 TB/s in all; 2.2
+// times that where everything sits in the Infinity Cache), if that is longer;
+// the last round of blocks counts in full.  Where a pass does not fill the
+// device, fewer blocks leave room for another context's (three contexts in
+// turn, 48^3: chunks of one plane 3.3 us per step, of two 2.1, and 4.4 for
+// either alone): the blocks of a full device count 0.6 more.
+Pass plan_pass(const int N[3], int mode, int hook, int T, int cus)
+{
+    Pass best;
+    const bool cached = fits_cache(mode, (double)N[0] * N[1] * N[2]);
+    const Shape* const all = hook == kUpdate ? kShapes : kHookedShapes;
+    const int n = (int)(hook == kUpdate ? sizeof(kShapes) : sizeof(kHookedShapes)) / (int)sizeof(Shape);
+    for (int i = 0; i < n; ++i) {
+        const Shape& v = all[i];
+        if (v.T != T || v.mode != mode || v.hook != hook || (v.whole && N[2] != 64)) continue;
+        const int rows = v.R * v.W, vz = v.whole ? 64 : 64 - 2 * T, vy = rows - 2 * T;
+        Pass p;
+        p.s = &v;
+        p.index = i;
+        p.gz = (N[2] + vz - 1) / vz;
+        p.gy = (N[1] + vy - 1) / vy;
+        const long long base = (long long)p.gz * p.gy;
+        int last = 0;
+        for (int q = 1; q <= std::min(N[0], 1024); ++q) {
+            const int xc = (N[0] + q - 1) / q;
+            if (xc == last) continue;
+            last = xc;
+            const long long nt = base * ((N[0] + xc - 1) / xc);
+            const double us = ((double)((nt + cus - 1) / cus) * round_us(mode, rows, T, xc, cached) + 3.0) *
+                              (1.0 + 0.6 * std::min(1.0, (double)nt / cus));
+            if (us < p.us) {
+                p.us = us;
+                p.xchunk = xc;
+                p.ntiles = nt;
+            }
+            if (nt > 64LL * cus) break;
+        }
+        if (p.us < best.us) best = p;
+    }
+    return best;
+}
+
+long long mark_words(const Pass& p)
+{
+    if (!p.s) return 0;
+    const long long groups = ((p.ntiles + kXCD - 1) / kXCD + kPaceGroup - 1) / kPaceGroup * kXCD;
+    return groups * ((p.xchunk + 2 * p.s->T) / kPacePlanes + 1);
+}
+
+long long most_mark_words(const int N[3], int cus)
+{
+    long long words = 0;
+    for (int mode = 0; mode < kModes; ++mode)
+        for (int T = 1; T <= kMaxT; ++T) words = std::max(words, mark_words(plan_pass(N, mode, kUpdate, T, cus)));
+    return words;
+}
+
+}  // namespace sweep
+}  // namespace fdtd

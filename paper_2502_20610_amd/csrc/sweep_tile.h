@@ -36,26 +36,12 @@
 #pragma once
 
 #include "fdtd_internal.h"
+#include "sweep_plan.h"
 
 namespace fdtd {
 namespace sweep {
 
-constexpr int kXCD = 8;          // XCDs of the device
-constexpr int kPaceGroup = 32;   // blocks an XCD runs at once (one per CU)
-constexpr int kPacePlanes = 4;   // planes between two progress marks
 constexpr unsigned kDropped = 0x80000000u;  // a buffer offset past every plane: the access is dropped
-
-constexpr int kMaxT = 5;         // steps of a pass
-
-enum { kArrays = 0, kLossy = 1, kTable = 2, kLossyTable = 3 };
-// What a pass computes: the update; the update with what the forward run of
-// the adjoint takes from it (monitor transform, design-box history); the
-// transposed half-steps of the reverse run,
-//   lE = A (.) lE - cH CH(lH),  lH += CE(cE (.) lE),
-// with the monitor samples of the step added to lE and lE recorded over the
-// design box, or without either.  A block that meets neither box runs the
-// plain form of its pass.
-enum { kUpdate = 0, kForward = 1, kReverse = 2, kTransposed = 3 };
 
 // Level l of a pass is step n + l (forward) or n - l (reverse).  A cell of the
 // design box, and in the forward run of the monitor box, belongs to the lane
@@ -90,31 +76,12 @@ struct SweepArgs {
     int pace_words;
 };
 
-// Tile shapes: T steps per pass, R rows per lane, W wavefronts.
-struct Variant {
-    int T, R, W, mode;
-    bool whole;  // for grids whose z axis is one wavefront
-    int hook;
-    void (*kern)(const SweepArgs);                    // (hook kUpdate)
-    void (*hooked)(const SweepArgs, const HookArgs);  // (the others)
-};
-
-// One pass of T steps over a grid: the tile shape and the split of x.
-struct Pass {
-    const Variant* v = nullptr;
-    int xchunk = 0, gz = 0, gy = 0;
-    long long ntiles = 0;
-    double us = 1e300;  // estimated
-};
-
-// The shapes of the adjoint's passes (sweep_adjoint.hip).
-const Variant* hooked_variants(int* n);
+// The kernels of the adjoint's passes, in the order of their shapes
+// (sweep_adjoint.hip).
+using HookedKernel = void (*)(const SweepArgs, const HookArgs);
+HookedKernel hooked_kernel_of(int index);
 // Coefficients a context's sweeps read.
 int mode_of(const fdtd_ctx* c);
-// Time of one round of blocks of `rows` rows over xc planes, us: the larger of
-// what the levels and what the memory take.
-double round_us(int mode, int rows, int T, int xc, bool cached);
-bool fits_cache(int mode, double cells);
 SweepArgs base_args(const fdtd_ctx* ctx);
 
 }  // namespace sweep

@@ -1,0 +1,60 @@
+"""Sweeps of grids past 1 GiB of state, whose blocks are kept in step by progress
+marks: changes of the coefficients between calls (table, arrays, conductive,
+material indices off), bit for bit against single steps of the plain scheme,
+which update in place."""
+import pytest
+
+from paper_2502_20610_amd import fdtd
+from tests.test_gpu_sweep import PEC, PER
+
+pytestmark = pytest.mark.gpu
+
+
+def _materials(kind, shape, gen):
+    import torch
+    few = torch.randint(0, 5, shape, device="cuda", generator=gen)
+    if "arrays" in kind:
+        eps = 1.0 + torch.rand(shape, device="cuda", generator=gen)
+    else:
+        eps = torch.tensor([1.0, 2.08, 3.5, 7.0, 12.25], device="cuda")[few]
+    sigma = None
+    if "lossy" in kind:
+        sigma = torch.tensor([0.0, 0.01, 0.1, 0.3, 0.4], device="cuda")[few].contiguous()
+    return eps.contiguous(), sigma
+
+
+@pytest.mark.parametrize("bc", [(PEC, PEC, PEC), (PER, PEC, PER)])
+def test_materials_change_between_sweeps(bc):
+    import torch
+    shape = (361, 360, 352)
+    assert 24 * shape[0] * shape[1] * shape[2] > 2 ** 30
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    fields = [torch.rand(shape, device="cuda", generator=gen) - 0.5 for _ in range(6)]
+    sims = [fdtd.Simulation(shape, 0.5, 1.0, bc, scheme="plain") for _ in range(2)]
+    try:
+        for sim in sims:
+            sim.set_fields(fields)
+            sim.synchronize()
+        swept, stepped = sims
+        for kind in ("table", "lossy arrays", "lossy table", "arrays", "table"):
+            eps, sigma = _materials(kind, shape, gen)
+            torch.cuda.synchronize()
+            for sim in sims:
+                sim.set_materials(eps, sigma=sigma)
+            for ids in (1, 0):
+                swept.set_option(fdtd.OPT_MATERIAL_IDS, ids)
+                swept.step(9)
+                for _ in range(9):
+                    stepped.step(1)
+                got, want = torch.empty(shape, device="cuda"), torch.empty(shape, device="cuda")
+                torch.cuda.synchronize()
+                for c in range(6):
+                    swept.read_fields(mask=1 << c, out=[got] * 6)
+                    stepped.read_fields(mask=1 << c, out=[want] * 6)
+                    swept.synchronize()
+                    stepped.synchronize()
+                    assert torch.equal(got.view(torch.int32), want.view(torch.int32)), (kind, ids, c)
+    finally:
+        for sim in sims:
+            sim.close()
