@@ -185,6 +185,38 @@ bool merge(const Plan* const* plans, int n, Merged* out, std::string* err)
     return true;
 }
 
+long long distance_bound(const int N[3], const int per[3], const int W[3], int K)
+{
+    // A consumer lies at most one layer per PEC axis below its producer, ring
+    // groups are whole within a layer, and a layer of a smaller box is part of
+    // the same layer of a larger one: so the box may be the largest of any band.
+    std::vector<long long> layer(1, 1);
+    long long ring = 1;
+    int axes = 0;
+    for (int d = 0; d < 3; ++d) {
+        if (per[d]) {
+            ring *= (N[d] + W[d] - 1) / W[d];
+            continue;
+        }
+        ++axes;
+        const int n = (N[d] + K + W[d] - 3) / W[d] + 2;
+        std::vector<long long> next(layer.size() + n - 1, 0);
+        for (size_t q = 0; q < next.size(); ++q) {
+            next[q] = q ? next[q - 1] : 0;
+            if (q < layer.size()) next[q] += layer[q];
+            if (q >= (size_t)n && q - n < layer.size()) next[q] -= layer[q - n];
+        }
+        layer.swap(next);
+    }
+    long long most = 0;
+    for (size_t q = 0; q < layer.size(); ++q) {
+        long long sum = 0;
+        for (size_t r = q; r < layer.size() && r <= q + axes; ++r) sum += layer[r];
+        most = std::max(most, sum);
+    }
+    return most * ring;
+}
+
 double band_cost(const int N[3], const int per[3], const int W[3], int K)
 {
     // Per cell update, a band of K steps costs the tile-steps that cover its

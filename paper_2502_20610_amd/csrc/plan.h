@@ -76,6 +76,10 @@ struct Merged {
 
 bool merge(const Plan* const* plans, int n, Merged* out, std::string* err);
 
+// An upper bound of Merged::D for one grid in bands of K steps, whatever the
+// call's length, from the sizes of the depth layers alone (no plan is built).
+long long distance_bound(const int N[3], const int per[3], const int W[3], int K);
+
 // Band-length cost model: relative cost per cell update of bands of K steps
 // on a grid (tile-steps covering the band's skewed space-time region, times
 // the band's start and end), see the definition.

@@ -1436,6 +1436,10 @@ void axes_of(const fdtd_ctx* c, int N[3], int per[3])
     for (int d = 0; d < 3; ++d) per[d] = c->cfg.bc[d] == FDTD_BC_PERIODIC;
 }
 
+// One component of a y or z face block: one row per x slot rounded up to four,
+// at least 16, x 16 words.
+size_t face_yz_bytes(int wx) { return (size_t)std::max(16, (wx + 1 + 3) & ~3) * 16 * sizeof(float); }
+
 // The plan of one context: tiles per band, tickets in topological order.
 int build_plan(fdtd_ctx* ctx, SystolicState* s, int nsteps, int K)
 {
@@ -1578,7 +1582,10 @@ bool wide_tile_ok(fdtd_ctx* const* cs, int n)
 //   * calls with a systolic option of their own, which ask for that kernel;
 //   * FP16 storage with more than 256 materials (with a table, the bands are
 //     swept over FP32 copies of the state and rounded where they end: the same
-//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 18.1 ms);
+//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 18.1 ms),
+//     and where the face rings of the band may not fit their 32-bit offsets:
+//     the launch then takes a shorter one, and rounds where that ends
+//     (1024^3: 49 steps instead of 64);
 //   * single steps (a sweep would leave the state in the other arrays);
 //   * on all-PEC grids, calls of two 64-step bands or more (512^3 and up by
 //     the band model), whose band and ring slots FDTD_INFO_* reports
@@ -1598,9 +1605,16 @@ bool sweeps_instead(fdtd_ctx* ctx, int64_t nsteps)
     for (int d = 0; d < 3; ++d)
         if (per[d]) group *= (N[d] + W[d] - 1) / W[d];
     int cus = 0;
-    if (group > 1 &&
-        (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || group > 2LL * cus))
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) {
+        (void)hipGetLastError();
         return false;
+    }
+    if (group > 2LL * cus) return false;
+    if (ctx->storage == FDTD_FP16_STORAGE) {
+        const int K = default_band(&ctx, 1, nsteps);
+        const double slots = (double)plan::distance_bound(N, per, W, K) + 2.0 * (2.0 * cus);
+        if (slots * K * 6.0 * (double)face_yz_bytes(W[0]) >= 4294967296.0) return false;
+    }
     if (!(per[0] || per[1] || per[2]) && nsteps >= 2 * kMaxBand && default_band(&ctx, 1, nsteps) == kMaxBand)
         return false;
     return sweep_ready(ctx);
@@ -1731,7 +1745,7 @@ int launch(fdtd_ctx* const* cs, int n, int64_t nsteps, int kcap = kMaxBand, bool
     // (one component of an x face block is 16 x 16 words; of a y or z face
     // block, one row per x slot rounded up to four, at least 16, x 16)
     const size_t face = (size_t)(4 * kNW) * 16 * sizeof(float);
-    const size_t face_yz = (size_t)std::max(16, (wx + 1 + 3) & ~3) * 16 * sizeof(float);
+    const size_t face_yz = face_yz_bytes(wx);
     const size_t rf6 = (size_t)R * Kmax * 6 * face_yz;
     // the z face's coefficients: cE (with conductivity ca too; with the wide
     // tile the index alone)

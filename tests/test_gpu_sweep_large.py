@@ -58,3 +58,38 @@ def test_materials_change_between_sweeps(bc):
     finally:
         for sim in sims:
             sim.close()
+
+
+def test_half_storage_rounds_where_the_rings_allow():
+    """FP16 storage on the largest grid, 64 steps with the automatic band: the face
+    rings of a 64-step band would pass 32-bit offsets, so the fields are rounded
+    after a shorter one, as with that band asked for."""
+    import torch
+    shape = (1024, 1024, 1024)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    field = torch.rand(shape, device="cuda", generator=gen) - 0.5
+    torch.cuda.synchronize()
+    sims, band = [], 0
+    try:
+        for _ in range(2):
+            sim = fdtd.Simulation(shape, 0.5, 1.0, (PEC, PEC, PEC), scheme="systolic", storage="fp16")
+            sims.append(sim)
+            if band:
+                sim.set_option(fdtd.OPT_BAND_STEPS, band)
+            sim.set_fields([field] * 6)
+            sim.step(64)
+            assert band in (0, sim.info(fdtd.INFO_SYSTOLIC_BAND))
+            band = sim.info(fdtd.INFO_SYSTOLIC_BAND)
+            assert band < 64
+        want = torch.empty(shape, device="cuda")
+        torch.cuda.synchronize()
+        for c in range(6):
+            sims[0].read_fields(mask=1 << c, out=[field] * 6)
+            sims[1].read_fields(mask=1 << c, out=[want] * 6)
+            for sim in sims:
+                sim.synchronize()
+            assert torch.equal(field.view(torch.int32), want.view(torch.int32)), c
+    finally:
+        for sim in sims:
+            sim.close()
