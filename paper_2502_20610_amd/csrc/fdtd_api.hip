@@ -9,6 +9,7 @@
 #include <string>
 
 #include "fdtd_internal.h"
+#include "ranges.h"
 
 using namespace fdtd;
 
@@ -902,19 +903,27 @@ int fdtd_read_fields(fdtd_ctx* ctx, uint32_t comp_mask, float* const dst[6], int
         (void)hipGetLastError();
         return fail(ctx, FDTD_ENOMEM, "read_fields: staging allocation failed");
     }
-    // one launch for arrays on this device; copies, which take or refuse any
-    // pointer, for others (and in a captured stream)
+    // one launch for arrays on this device, each whole within its allocation and
+    // none over another; copies, which take or refuse any pointer and are done
+    // in turn, for others (and in a captured stream)
     bool here = !h16 && where == FDTD_DEVICE && comp_mask && !stream_capturing(ctx);
+    uintptr_t to[6], base[6];
+    size_t size[6];
+    int m = 0;
     for (int c = 0; c < 6 && here; ++c) {
         hipPointerAttribute_t at;
+        hipDeviceptr_t b = nullptr;
         if (!(comp_mask >> c & 1u)) continue;
         here = hipPointerGetAttributes(&at, dst[c]) == hipSuccess && at.type == hipMemoryTypeDevice &&
-               at.device == ctx->device;
+               at.device == ctx->device && hipMemGetAddressRange(&b, &size[m], dst[c]) == hipSuccess;
         if (!here) (void)hipGetLastError();
+        base[m] = (uintptr_t)b;
+        to[m++] = (uintptr_t)dst[c];
     }
+    here = here && writable_at_once(to, base, size, m, bytes);
     if (here) {
         Arrays6 A{};
-        unsigned m = 0;
+        m = 0;
         uintptr_t bits = (uintptr_t)ctx->ncell * sizeof(float);  // a whole number of 16-byte moves?
         for (int c = 0; c < 6; ++c) {
             if (!(comp_mask >> c & 1u)) continue;
@@ -924,7 +933,7 @@ int fdtd_read_fields(fdtd_ctx* ctx, uint32_t comp_mask, float* const dst[6], int
         }
         const bool wide = bits % sizeof(float4) == 0;
         const long long n = wide ? ctx->ncell / 4 : ctx->ncell;
-        const dim3 grid((unsigned)std::max<long long>(1, std::min<long long>((n + 4 * kThreads - 1) / (4 * kThreads), 2048)), m);
+        const dim3 grid((unsigned)std::max<long long>(1, std::min<long long>((n + 4 * kThreads - 1) / (4 * kThreads), 2048)), (unsigned)m);
         if (wide)
             hipLaunchKernelGGL(copy_fields_kernel<float4>, grid, dim3(kThreads), 0, ctx->stream, A, n);
         else

@@ -26,3 +26,11 @@ def test_ring_distance_bound_under_address_and_undefined_sanitizers(tmp_path):
     subprocess.run(["g++", "-std=c++17"] + SAN + ["-I" + CSRC, os.path.join(CSRC, "plan.cpp"),
                     os.path.join(ROOT, "tests", "sanitize", "ring_check.cpp"), "-o", exe], check=True)
     assert "ring checks passed" in _run(exe)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_array_ranges_under_address_and_undefined_sanitizers(tmp_path):
+    exe = str(tmp_path / "ranges_check")
+    subprocess.run(["g++", "-std=c++17"] + SAN + ["-I" + CSRC, os.path.join(ROOT, "tests", "sanitize", "ranges_check.cpp"),
+                    "-o", exe], check=True)
+    assert "range checks passed" in _run(exe)
