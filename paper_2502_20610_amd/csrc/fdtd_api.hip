@@ -292,10 +292,20 @@ int rebuild_dev_sources(fdtd_ctx* ctx)
         const SourceRec& s = ctx->sources[q];
         h[q] = DevSource{s.comp, s.i, s.j, s.k, (long long)s.len, (long long)s.first, s.wave};
     }
-    hipError_t e = hipMalloc(&ctx->dev_sources, h.size() * sizeof(DevSource));
+    std::stable_sort(h.begin(), h.end(), [](const DevSource& x, const DevSource& y) { return x.i < y.i; });
+    std::vector<int> plane;
+    if (h.size() > (size_t)kListedSources && ctx->nx <= kMaxIndexedPlanes) {
+        plane.assign((size_t)ctx->nx + 1, 0);
+        for (const DevSource& s : h) ++plane[s.i + 1];
+        for (int i = 0; i < ctx->nx; ++i) plane[i + 1] += plane[i];
+    }
+    const size_t bytes = h.size() * sizeof(DevSource);
+    hipError_t e = hipMalloc(&ctx->dev_sources, bytes + plane.size() * sizeof(int));
     if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc(sources)");
-    e = hipMemcpyAsync(ctx->dev_sources, h.data(), h.size() * sizeof(DevSource),
-                       hipMemcpyHostToDevice, ctx->stream);
+    e = hipMemcpyAsync(ctx->dev_sources, h.data(), bytes, hipMemcpyHostToDevice, ctx->stream);
+    if (e == hipSuccess && !plane.empty())
+        e = hipMemcpyAsync(ctx->dev_sources + h.size(), plane.data(), plane.size() * sizeof(int), hipMemcpyHostToDevice,
+                           ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipMemcpyAsync(sources)");
     e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");

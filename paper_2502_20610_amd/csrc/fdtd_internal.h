@@ -66,7 +66,11 @@ struct fdtd_ctx {
     float cH;
 
     std::vector<fdtd::SourceRec> sources;
-    fdtd::DevSource* dev_sources;  // device table, rebuilt when sources change
+    // device table, rebuilt when sources change: ordered by plane, the sources
+    // of a plane in the order they were added; then, with more than
+    // kListedSources and at most kMaxIndexedPlanes planes, the first source of
+    // each plane (nx + 1 ints)
+    fdtd::DevSource* dev_sources;
     int dev_sources_n;
 
     int64_t step_count;
@@ -121,6 +125,8 @@ struct fdtd_ctx {
 
 namespace fdtd {
 
+constexpr int kListedSources = 64;          // of which a sweep's block keeps a list
+constexpr int kMaxIndexedPlanes = 1 << 22;  // 16 MB of index
 constexpr int64_t kDefaultSpinLimit = int64_t(1) << 22;
 
 // Error helpers (set ctx->err, return the code).

@@ -154,9 +154,11 @@ SweepArgs sweep::base_args(const fdtd_ctx* ctx)
     return A;
 }
 
-// A plane must fit a buffer descriptor with room for the dropped offset.
+// A plane must fit a buffer descriptor with room for the dropped offset, and
+// many sources need their index of planes.
 bool sweep_supported(const fdtd_ctx* ctx)
 {
+    if (ctx->dev_sources_n > kListedSources && ctx->nx > kMaxIndexedPlanes) return false;
     // (FP16 storage: with the coefficients' exact values in a table)
     return (ctx->storage == FDTD_FP32 || mode_of(ctx) == kTable) && (uint64_t)ctx->ny * (uint64_t)ctx->nz * 4u < (uint64_t)kDropped;
 }

@@ -93,3 +93,40 @@ def test_half_storage_rounds_where_the_rings_allow():
     finally:
         for sim in sims:
             sim.close()
+
+
+@pytest.mark.parametrize("shape,bc", [((30, 40, 70), (PER, PER, PEC)), ((70, 37, 33), (PEC, PER, PER)), ((3, 50, 64), (PER, PER, PER))])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_a_plane_of_sources(shape, bc, axis):
+    """A source on every cell of a plane (two on some, starting at different
+    steps, added in no order of planes), as one scheme after another takes them:
+    more than a block keeps at hand, against the FP32 oracle."""
+    import numpy as np
+
+    import oracle
+    from paper_2502_20610_amd import workloads as wl
+    from tests.test_gpu_parity import assert_bitwise
+    rng = np.random.default_rng(sum(shape) + axis)
+    eps = rng.choice(np.float32([1.0, 2.08, 7.0]), shape)
+    zero = [np.zeros(shape, np.float32) for _ in range(6)]
+    cells = np.argwhere(np.ones([1 if a == axis else n for a, n in enumerate(shape)]))
+    cells[:, axis] = shape[axis] // 2
+    cells = cells[[all(bc[a] == PER or p[a] > 0 for a in range(3)) for p in cells]]
+    cells = cells[rng.permutation(len(cells))][:600]
+    cells = np.concatenate([cells, cells[:40]])
+    sources = [wl.dipole(int(rng.integers(0, 3)), *(int(v) for v in p), rng.uniform(-1, 1, 9).astype(np.float32),
+                         first_step=int(rng.integers(0, 4))) for p in cells]
+    assert len(sources) > 64
+    for scheme in ("plain", "plain_fused"):
+        sim = fdtd.Simulation(shape, 0.5, 1.0, bc, scheme=scheme)
+        try:
+            sim.set_materials(eps)
+            for s in sources:
+                sim.add_source(s["comp"], s["i"], s["j"], s["k"], s["waveform"], s["first_step"])
+            for n in (1, 6, 8):
+                sim.step(n)
+            got = sim.read_fields()
+        finally:
+            sim.close()
+        ref = oracle.run(zero, [eps] * 3, bc, 0.5, 1.0, 15, sources=sources, dtype=np.float32)
+        assert_bitwise(got, ref, "%s %s axis %d" % (scheme, shape, axis))
