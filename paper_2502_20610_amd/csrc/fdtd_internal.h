@@ -153,6 +153,9 @@ bool plain_sweeps(const fdtd_ctx* ctx, int64_t nsteps);
 // Fused plain scheme (plain.hip).
 int plain_fused_step(fdtd_ctx* ctx, int64_t nsteps);
 int plain_fused_prepare(fdtd_ctx* ctx);
+// Launch one step (ctx->step_count) from the arrays `in` into `out`: the pass of
+// one step of the fused scheme, and of sweeps where it is the faster (plain.hip).
+int fused_one_step(fdtd_ctx* ctx, float* const in[6], float* const out[6]);
 
 // Sweep: several steps per pass into the second field set, whose pointers
 // trade places with ctx->field after every pass (sweep.hip).

@@ -37,6 +37,7 @@ struct SweepState {
     int cus = 0;
     int mode = -1;
     Pass pass[kMaxT + 1];    // the plan of a pass of T steps, for `mode`
+    bool fused = false;      // a pass of one step as a launch of the fused step
     int hooked_mode = -1;
     Pass forward[kMaxT + 1], reverse[kMaxT + 1];  // of the adjoint's passes
     unsigned* pace = nullptr;
@@ -70,17 +71,32 @@ int state(fdtd_ctx* ctx)
     return FDTD_OK;
 }
 
-int plan(fdtd_ctx* ctx)
+// The passes for the coefficients the context has now.
+int plan_passes(fdtd_ctx* ctx)
 {
     int rc = state(ctx);
     if (rc) return rc;
     SweepState* S = ctx->sweep;
     const int mode = mode_of(ctx);
     const int N[3] = {ctx->nx, ctx->ny, ctx->nz};
-    if (S->mode != mode) {
-        for (int T = 1; T <= kMaxT; ++T) S->pass[T] = plan_pass(N, mode, kUpdate, T, S->cus);
-        S->mode = mode;
-    }
+    if (S->mode == mode) return FDTD_OK;
+    for (int T = 1; T <= kMaxT; ++T) S->pass[T] = plan_pass(N, mode, kUpdate, T, S->cus);
+    // a pass of one step is the fused step's launch where that is the faster
+    // (256^3 arrays 245 / 345 us, 128^3 conductive arrays 32 / 52)
+    S->fused = one_step_us(N, ctx->ca[0] != nullptr) < alone_us(S->pass[1], N, S->cus);
+    S->mode = mode;
+    return FDTD_OK;
+}
+
+// (its blocks read every source on every plane)
+bool one_step_launch(const fdtd_ctx* ctx) { return ctx->sweep->fused && ctx->dev_sources_n <= 8; }
+
+int plan(fdtd_ctx* ctx)
+{
+    int rc = plan_passes(ctx);
+    if (rc) return rc;
+    SweepState* S = ctx->sweep;
+    const int N[3] = {ctx->nx, ctx->ny, ctx->nz};
     // Blocks are kept in step where the state is past 1 GiB: 512^3, T = 5,
     // 225 -> 256 G cell updates/s, 1024 x 1024 x 512 255 -> 269; at 256^3,
     // one round of blocks, 202 against 205.  The marks are allocated once, for
@@ -198,7 +214,7 @@ int sweep_prepare(fdtd_ctx* ctx)
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 *p = nullptr;
-                return fail(ctx, FDTD_ENOMEM, "fused plain step: second field set does not fit");
+                return fail(ctx, FDTD_ENOMEM, "the second field set does not fit");
             }
         }
     return plan(ctx);
@@ -242,8 +258,13 @@ int run(fdtd_ctx* ctx, float* now[6], float* other[6], int64_t n, int kernel, bo
         if (paced) S->turn ^= 1;
         PendingTiming t;
         timing_begin(ctx, kernel, &t);
-        launch_pass(ctx, P, A);
+        int rc = FDTD_OK;
+        if (T == 1 && ctx->storage == FDTD_FP32 && one_step_launch(ctx))
+            rc = fused_one_step(ctx, now, other);
+        else
+            launch_pass(ctx, P, A);
         timing_end(ctx, &t);
+        if (rc) return rc;
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(ctx, e, "launch(sweep)");
         for (int c = 0; c < 6; ++c) std::swap(now[c], other[c]);

@@ -23,13 +23,25 @@ int in_bytes(int mode) { return 24 + (mode == kArrays ? 12 : mode == kLossy ? 24
 
 bool fits_cache(int mode, double cells) { return (24.0 + in_bytes(mode)) * cells <= 256e6; }
 
-double round_us(int mode, int rows, int T, int xc, bool cached)
+namespace {
+
+// As round_us for tiles of `rows` rows that touch `met` rows and `lanes` lanes
+// of the grid.
+double tile_us(int mode, int rows, int T, int xc, bool cached, int met, int lanes)
 {
     const double level = 0.11 + 0.29 * rows / 16.0;
-    const double bytes = rows * 64.0 * in_bytes(mode) + (rows - 2 * T) * (64 - 2 * T) * 24.0;
+    const double out = (double)std::max(1, std::min(met, rows - 2 * T)) * std::min(lanes, 64 - 2 * T);
+    const double bytes = (double)met * lanes * in_bytes(mode) + out * 24.0;
     // (level l starts at iteration 2l)
     const double compute = 0.45 * (xc + 2 * T) + level * (T * (T + 1) + (double)xc * T);
     return std::max(compute, bytes / (cached ? 2.2 * 17600.0 : 17600.0) * (xc + 2 * T));
+}
+
+}  // namespace
+
+double round_us(int mode, int rows, int T, int xc, bool cached)
+{
+    return tile_us(mode, rows, T, xc, cached, rows, 64);
 }
 
 // The model of a block's time, fitted to passes measured from 32^3 to 1024 x
@@ -75,6 +87,23 @@ Pass plan_pass(const int N[3], int mode, int hook, int T, int cus)
         if (p.us < best.us) best = p;
     }
     return best;
+}
+
+double alone_us(const Pass& p, const int N[3], int cus)
+{
+    const int rows = p.s->R * p.s->W;
+    const bool cached = fits_cache(p.s->mode, (double)N[0] * N[1] * N[2]);
+    const double round = tile_us(p.s->mode, rows, p.s->T, p.xchunk, cached, std::min(rows, N[1] + 8), std::min(64, N[2] + 16));
+    return ((double)((p.ntiles + cus - 1) / cus) * round + 3.0) * (1.0 + 0.2 * std::min(1.0, (double)p.ntiles / cus));
+}
+
+double one_step_us(const int N[3], bool lossy)
+{
+    // 256^3 247 us (conductive 277), 384^3 749 (876), 512^3 1921 (2317); 64^3 and
+    // below 22 (5); thin along z 0.55 (0.33) ns per row of 64 lanes
+    const double cells = (double)N[0] * N[1] * N[2];
+    const double waves = (double)N[0] * ((N[1] + 6) / 7 * 8) * ((N[2] + 63) / 64);
+    return lossy ? std::max(4.0 + 72.0 * cells / 4.3e6, waves * 0.00033) : std::max(25.0 + 60.0 * cells / 4.2e6, waves * 0.00055);
 }
 
 long long mark_words(const Pass& p)

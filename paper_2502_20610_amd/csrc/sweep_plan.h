@@ -66,6 +66,12 @@ double round_us(int mode, int rows, int T, int xc, bool cached);
 // (s null: no shape has that T).
 Pass plan_pass(const int N[3], int mode, int hook, int T, int cus);
 
+// Estimates by which a call chooses between a sweep and another launch: a pass
+// alone on the device, counting what its tiles touch of a thin grid; one step
+// in one launch (plain.hip).
+double alone_us(const Pass& p, const int N[3], int cus);
+double one_step_us(const int N[3], bool lossy);
+
 // Words of progress marks that a pass of this plan addresses, and the most that
 // any plan of the grid does, whatever coefficients the context is given.
 long long mark_words(const Pass& p);

@@ -130,3 +130,35 @@ def test_a_plane_of_sources(shape, bc, axis):
             sim.close()
         ref = oracle.run(zero, [eps] * 3, bc, 0.5, 1.0, 15, sources=sources, dtype=np.float32)
         assert_bitwise(got, ref, "%s %s axis %d" % (scheme, shape, axis))
+
+
+@pytest.mark.parametrize("shape,bc,lossy", [((250, 240, 256), (PEC, PEC, PEC), False), ((97, 130, 129), (PER, PEC, PER), True)])
+def test_single_fused_steps(shape, bc, lossy):
+    """Calls of one step on the fused scheme (one launch of its own on these
+    grids), bit for bit as steps of the plain scheme in place."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    eps, sigma = _materials("lossy arrays" if lossy else "arrays", shape, gen)
+    fields = [torch.rand(shape, device="cuda", generator=gen) - 0.5 for _ in range(6)]
+    torch.cuda.synchronize()
+    sims = [fdtd.Simulation(shape, 0.5, 1.0, bc, scheme=s) for s in ("plain_fused", "plain")]
+    try:
+        for sim in sims:
+            sim.set_materials(eps, sigma=sigma)
+            sim.set_fields(fields)
+            sim.add_source(2, *(n // 2 for n in shape), [0.5, -1.0, 2.0], 1)
+            for _ in range(5):
+                sim.step(1)
+            sim.synchronize()
+        got, want = torch.empty(shape, device="cuda"), torch.empty(shape, device="cuda")
+        torch.cuda.synchronize()
+        for c in range(6):
+            sims[0].read_fields(mask=1 << c, out=[got] * 6)
+            sims[1].read_fields(mask=1 << c, out=[want] * 6)
+            for sim in sims:
+                sim.synchronize()
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32)), c
+    finally:
+        for sim in sims:
+            sim.close()
