@@ -415,11 +415,20 @@ enum {
                                  15.  Conductive grids always take 11; FP16
                                  storage takes 15 or 19.  A batch needs one
                                  width for all.                                */
-    FDTD_OPT_AUTOTUNE_PLAIN = 8 /* 1 = fdtd_autotune also times the plain
+    FDTD_OPT_AUTOTUNE_PLAIN = 8,/* 1 = fdtd_autotune also times the plain
                                  two-launch scheme (FP32 storage only, where
                                  every scheme gives the same bits) and switches
                                  the context to it when it is faster; 0
                                  (default) = systolic configurations only     */
+    FDTD_OPT_SWEEPS = 9       /* 1 (default) = calls may run as sweeps (see the
+                                 schemes above); 0 = every scheme by its own
+                                 launches (plain: one per half-step; fused: one
+                                 per step; systolic: the persistent one;
+                                 fdtd_adjoint: one-step kernels), and the second
+                                 field set and FP16 storage's FP32 copies are
+                                 given back, after waiting for the stream (the
+                                 fused scheme takes its set again when it next
+                                 runs).  Same results.                        */
 };
 
 /* Set a tuning option (see FDTD_OPT_*).  FDTD_EINVAL for unknown options or

@@ -487,6 +487,7 @@ int fdtd_create(const fdtd_config* cfg, fdtd_ctx** out)
     ctx->spin_limit = kDefaultSpinLimit;
     ctx->profile = false;
     ctx->use_mat = true;
+    ctx->use_sweeps = true;
     ctx->use_graphs = true;
     ctx->cH = (float)(cfg->dt / cfg->dx);
     ctx->err = "no error";
@@ -1105,6 +1106,14 @@ int fdtd_set_option(fdtd_ctx* ctx, int option, int64_t value)
     case FDTD_OPT_MATERIAL_IDS:
         if (value != 0 && value != 1) return fail(ctx, FDTD_EINVAL, "set_option: material ids is 0 or 1");
         ctx->use_mat = value == 1;
+        return FDTD_OK;
+    case FDTD_OPT_SWEEPS:
+        if (value != 0 && value != 1) return fail(ctx, FDTD_EINVAL, "set_option: sweeps is 0 or 1");
+        ctx->use_sweeps = value == 1;
+        if (!ctx->use_sweeps && !stream_capturing(ctx)) {
+            (void)hipSetDevice(ctx->device);
+            sweep_give_back(ctx);
+        }
         return FDTD_OK;
     case FDTD_OPT_PROFILE:
         if (value != 0 && value != 1) return fail(ctx, FDTD_EINVAL, "set_option: profile is 0 or 1");

@@ -100,6 +100,7 @@ struct fdtd_ctx {
     float* mat_tab;   // kMaxMaterials x 3 floats, entry 0 = (+0, +0, +0)
     int nmat;
     bool use_mat;     // FDTD_OPT_MATERIAL_IDS
+    bool use_sweeps;  // FDTD_OPT_SWEEPS
     // the same as one byte per cell, and for conductive grids too: the table
     // then holds (cE, ca), 6 floats an entry; ntab8 = 0 when not available
     uint8_t* mat_id8;
@@ -164,6 +165,9 @@ bool sweep_supported(const fdtd_ctx* ctx);
 // is there, or fits well (and is then allocated).
 bool sweep_ready(fdtd_ctx* ctx);
 int sweep_prepare(fdtd_ctx* ctx);
+// Gives the second field set (and FP16 storage's FP32 copies) back; waits for
+// the context's stream.
+void sweep_give_back(fdtd_ctx* ctx);
 // Advance n steps; timed as `kernel`.  With `even` the state of a call of two
 // steps or more ends in the arrays it started from.
 int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);

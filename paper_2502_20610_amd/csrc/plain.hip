@@ -578,7 +578,7 @@ int plain_step(fdtd_ctx* ctx, int64_t nsteps)
 // 3.3 against 5.9 and 8.1 against 14.8).  A single step stays in place.
 bool plain_sweeps(const fdtd_ctx* ctx, int64_t nsteps)
 {
-    return nsteps > 1 && !ctx->profile && ctx->storage == FDTD_FP32 && sweep_supported(ctx);
+    return nsteps > 1 && ctx->use_sweeps && !ctx->profile && ctx->storage == FDTD_FP32 && sweep_supported(ctx);
 }
 
 // One step from `in` into `out` (fused step).
@@ -614,11 +614,11 @@ int plain_fused_step(fdtd_ctx* ctx, int64_t nsteps)
     int rc = plain_fused_prepare(ctx);
     if (rc) return rc;
     // (an even number of steps ends in the arrays it started from)
-    if (!ctx->profile && sweep_supported(ctx))
+    if (!ctx->profile && ctx->use_sweeps && sweep_supported(ctx))
         return sweep_steps(ctx, nsteps, FDTD_KERNEL_PLAIN_FUSED, nsteps % 2 == 0);
-    // one launch per step: per-kernel timing, a plane of 2 GiB or more
+    // one launch per step: per-kernel timing, sweeps off, a plane of 2 GiB or more
     for (int64_t q = 0; q < nsteps && rc == FDTD_OK; ++q) {
-        if (sweep_supported(ctx)) {
+        if (ctx->use_sweeps && sweep_supported(ctx)) {
             rc = sweep_steps(ctx, 1, FDTD_KERNEL_PLAIN_FUSED, false);
             continue;
         }

@@ -181,7 +181,7 @@ bool sweep_supported(const fdtd_ctx* ctx)
 
 bool sweep_ready(fdtd_ctx* ctx)
 {
-    if (!sweep_supported(ctx)) return false;
+    if (!ctx->use_sweeps || !sweep_supported(ctx)) return false;
     const bool half = ctx->storage == FDTD_FP16_STORAGE;
     bool have = true;
     for (int c = 0; c < 6; ++c) have = have && ctx->alt[c] && (!half || ctx->wide[c]);
@@ -196,12 +196,18 @@ bool sweep_ready(fdtd_ctx* ctx)
     }
     if ((half ? 48.0 : 24.0) * (double)ctx->ncell > 0.25 * (double)free_b) return false;
     if (sweep_prepare(ctx) == FDTD_OK) return true;
+    sweep_give_back(ctx);
+    return false;
+}
+
+void sweep_give_back(fdtd_ctx* ctx)
+{
+    (void)hipStreamSynchronize(ctx->stream);
     for (int c = 0; c < 6; ++c) {
         if (ctx->alt[c]) (void)hipFree(ctx->alt[c]);
         if (ctx->wide[c]) (void)hipFree(ctx->wide[c]);
         ctx->alt[c] = ctx->wide[c] = nullptr;
     }
-    return false;
 }
 
 int sweep_prepare(fdtd_ctx* ctx)

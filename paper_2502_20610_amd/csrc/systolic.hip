@@ -1595,7 +1595,7 @@ bool wide_tile_ok(fdtd_ctx* const* cs, int n)
 bool sweeps_instead(fdtd_ctx* ctx, int64_t nsteps)
 {
     if (nsteps < 2 || nsteps > (int64_t(1) << 24) || !sweep_supported(ctx)) return false;
-    if (ctx->band_steps || ctx->workgroups || ctx->tile_wx || ctx->spin_limit != kDefaultSpinLimit) return false;
+    if (!ctx->use_sweeps || ctx->band_steps || ctx->workgroups || ctx->tile_wx || ctx->spin_limit != kDefaultSpinLimit) return false;
     if (getenv("FDTD_SYSTOLIC_SYNC") || getenv("FDTD_SYSTOLIC_ORDER")) return false;
     ctx->auto_wx = wide_tile_ok(&ctx, 1) ? WX_WIDE : WX;
     int N[3], per[3], W[3];
