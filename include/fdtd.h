@@ -69,7 +69,11 @@
  *     call), for the whole grid; every exchange between tiles inside a band
  *     keeps FP32.
  * fdtd_read_fields returns the stored values times 2^e_c, exactly.  With FP16
- * storage, conductive materials and fdtd_adjoint return FDTD_EUNSUPPORTED. 
+ * storage, conductive materials and fdtd_adjoint return FDTD_EUNSUPPORTED.
+ * Memory: 18 bytes per cell for fields and coefficients, 5 for material
+ * indices, and, where the systolic scheme sweeps, 48 for two FP32 sets, taken
+ * by the first such call if they fit a sixteenth of the free device memory and
+ * kept until FDTD_OPT_SWEEPS = 0 or fdtd_destroy.
  *
  * Boundaries: indices are periodic on every axis; a PEC axis additionally
  * holds the two E components tangential to its planes at +0 on its index-0

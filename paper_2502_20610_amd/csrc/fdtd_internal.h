@@ -62,7 +62,7 @@ struct fdtd_ctx {
     int fexp[6];      // FP16 storage: power-of-two scale exponent per field component
     float* ca[3];     // E decay per step with conductivity; null when lossless
     float* alt[6];    // second field set of the sweeps (allocated on first use)
-    float* wide[6];   // FP16 storage: the first one, FP32 for the length of a call
+    float* wide[6];   // FP16 storage: the first one, in FP32 while a band runs (kept between calls)
     float cH;
 
     std::vector<fdtd::SourceRec> sources;
@@ -171,11 +171,11 @@ void sweep_give_back(fdtd_ctx* ctx);
 // Advance n steps; timed as `kernel`.  With `even` the state of a call of two
 // steps or more ends in the arrays it started from.
 int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even);
-// The longest pass, the blocks and the tiles of the last sweep of the context.
 // FP16 storage: advance n steps by sweeps over FP32 copies of the state,
 // rounded to binary16 after every `band` steps and at the end (both field sets
 // are allocated by sweep_ready).
 int sweep_half_steps(fdtd_ctx* ctx, int64_t n, int64_t band, int kernel);
+// The longest pass, the blocks and the tiles of the last sweep of the context.
 void sweep_shape(const fdtd_ctx* ctx, int* steps, int* blocks, int* tiles);
 void sweep_release(fdtd_ctx* ctx);
 // Advance the contexts by nsteps >= 2 each, one launch per pass for all, on

@@ -186,15 +186,18 @@ bool sweep_ready(fdtd_ctx* ctx)
     bool have = true;
     for (int c = 0; c < 6; ++c) have = have && ctx->alt[c] && (!half || ctx->wide[c]);
     if (have) return true;
-    // a scheme that can do without the second field set takes it only where
-    // three quarters of the free memory stay free
+    // A scheme that can do without the second field set takes it only where
+    // three quarters of the free memory stay free.  FP16 storage, which is there
+    // to hold larger grids, takes its two FP32 sets (48 B per cell next to 23 of
+    // its own) from a sixteenth: on an empty device up to 370 M cells.
     if (stream_capturing(ctx)) return false;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    if ((half ? 48.0 : 24.0) * (double)ctx->ncell > 0.25 * (double)free_b) return false;
+    if (half ? 48.0 * (double)ctx->ncell > 0.0625 * (double)free_b : 24.0 * (double)ctx->ncell > 0.25 * (double)free_b)
+        return false;
     if (sweep_prepare(ctx) == FDTD_OK) return true;
     sweep_give_back(ctx);
     return false;

@@ -139,3 +139,24 @@ def test_sweeps_off_gives_the_second_sets_back(storage, bytes_per_cell):
             sim.set_option(fdtd.OPT_SWEEPS, 2)
     finally:
         sim.close()
+
+
+def test_half_storage_takes_little_memory_for_sweeps():
+    """FP16 storage takes its FP32 sets from a sixteenth of the free memory; a grid
+    past that keeps the persistent launch and its own memory."""
+    import torch
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    for share, swept in ((1.0 / 12, False), (1.0 / 40, True)):
+        plane = 512 * 512
+        shape = (int(share * free / 48 / plane), 512, 512)
+        sim = fdtd.Simulation(shape, 0.5, 1.0, (PEC, PEC, PEC), scheme="systolic", storage="fp16")
+        try:
+            before = torch.cuda.mem_get_info()[0]
+            sim.step(8)
+            sim.synchronize()
+            taken = before - torch.cuda.mem_get_info()[0]
+            assert (sim.info(fdtd.INFO_RING_SLOTS) == 0) == swept
+            assert (taken > 24 * plane * shape[0]) == swept
+        finally:
+            sim.close()
