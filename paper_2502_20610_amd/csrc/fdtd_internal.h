@@ -150,7 +150,7 @@ void timing_end(fdtd_ctx* ctx, PendingTiming* t);
 int plain_step(fdtd_ctx* ctx, int64_t nsteps);
 // Whether a call of the plain scheme advances the grid by sweeps, given the
 // second field set (plain.hip).
-bool plain_sweeps(const fdtd_ctx* ctx, int64_t nsteps);
+bool plain_sweeps(fdtd_ctx* ctx, int64_t nsteps);
 // Fused plain scheme (plain.hip).
 int plain_fused_step(fdtd_ctx* ctx, int64_t nsteps);
 int plain_fused_prepare(fdtd_ctx* ctx);
@@ -164,6 +164,11 @@ bool sweep_supported(const fdtd_ctx* ctx);
 // Whether a scheme that does not need the second field set should sweep: it
 // is there, or fits well (and is then allocated).
 bool sweep_ready(fdtd_ctx* ctx);
+// Whether n steps by sweeps are estimated to take no longer than in place.
+bool sweeps_beat_in_place(fdtd_ctx* ctx, int64_t n);
+// Whether the systolic scheme keeps its persistent launch on a thin grid (and in
+// FP16 calls of two steps on periodic ones).
+bool sweeps_too_thin(const fdtd_ctx* ctx, int64_t n);
 int sweep_prepare(fdtd_ctx* ctx);
 // Gives the second field set (and FP16 storage's FP32 copies) back; waits for
 // the context's stream.

@@ -572,13 +572,17 @@ int plain_step(fdtd_ctx* ctx, int64_t nsteps)
     return run_steps(ctx, nsteps);
 }
 
-// Sweeps at every size: 32^3 5.3 us per step against 6.9 for replayed graphs
-// of the two launches, 64^3 6.0 against 8.2, 96^3 9.6 against 17.6, 256^3 80
-// against 302 (64-step calls; with three contexts in turn 2.0 against 4.6,
-// 3.3 against 5.9 and 8.1 against 14.8).  A single step stays in place.
-bool plain_sweeps(const fdtd_ctx* ctx, int64_t nsteps)
+// Sweeps at every ordinary size: 32^3 5.3 us per step against 6.9 for replayed
+// graphs of the two launches, 64^3 6.0 against 8.2, 96^3 9.6 against 17.6, 256^3
+// 80 against 302 (64-step calls; with three contexts in turn 2.0 against 4.6,
+// 3.3 against 5.9 and 8.1 against 14.8).  In place: a single step; two steps
+// past 2^17 cells, which would be two passes of one (128^3 75 / 90 us, 1024 x 4 x
+// 1024 117 / 195; 48^3 22 / 19); and where the estimates say so, thin grids
+// above all (1024 x 2 x 1024, 20 steps 680 / 1050 us, 4096 x 1 x 512 676 / 1830).
+bool plain_sweeps(fdtd_ctx* ctx, int64_t nsteps)
 {
-    return nsteps > 1 && ctx->use_sweeps && !ctx->profile && ctx->storage == FDTD_FP32 && sweep_supported(ctx);
+    return nsteps > 1 && ctx->use_sweeps && !ctx->profile && ctx->storage == FDTD_FP32 && sweep_supported(ctx) &&
+           (nsteps > 2 || ctx->ncell <= 1 << 17) && sweeps_beat_in_place(ctx, nsteps);
 }
 
 // One step from `in` into `out` (fused step).

@@ -284,6 +284,35 @@ int run(fdtd_ctx* ctx, float* now[6], float* other[6], int64_t n, int kernel, bo
 
 }  // namespace
 
+bool sweeps_too_thin(const fdtd_ctx* ctx, int64_t n)
+{
+    bool periodic = false;
+    for (int d = 0; d < 3; ++d) periodic = periodic || ctx->cfg.bc[d] == FDTD_BC_PERIODIC;
+    const bool half = ctx->storage == FDTD_FP16_STORAGE;
+    // (FP16 storage converts the state both ways in a dozen launches of their
+    // own: two steps on periodic 32^3 72 us persistent, 83 swept; closed 128 / 81)
+    if (half && periodic && n == 2) return true;
+    const int N[3] = {ctx->nx, ctx->ny, ctx->nz};
+    return thin_for_sweeps(N, periodic, mode_of(ctx), half, n);
+}
+
+bool sweeps_beat_in_place(fdtd_ctx* ctx, int64_t n)
+{
+    if (plan_passes(ctx) != FDTD_OK) return false;
+    const SweepState* S = ctx->sweep;
+    const int N[3] = {ctx->nx, ctx->ny, ctx->nz};
+    const int64_t passes = split(S->pass, n, n > 1);
+    if (passes == 0) return false;
+    auto pass_us = [&](int T) {
+        const double us = alone_us(S->pass[T], N, S->cus);
+        return T == 1 && one_step_launch(ctx) ? std::min(us, one_step_us(N, ctx->ca[0] != nullptr)) : us;
+    };
+    const int t = (int)(n / passes);
+    const int64_t longer = n % passes;
+    const double us = (double)(passes - longer) * pass_us(t) + (longer ? (double)longer * pass_us(t + 1) : 0.0);
+    return us <= 1.1 * in_place_us(N, ctx->ca[0] != nullptr, n);
+}
+
 int sweep_steps(fdtd_ctx* ctx, int64_t n, int kernel, bool even)
 {
     int rc = sweep_prepare(ctx);

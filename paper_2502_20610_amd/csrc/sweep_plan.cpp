@@ -97,6 +97,17 @@ double alone_us(const Pass& p, const int N[3], int cus)
     return ((double)((p.ntiles + cus - 1) / cus) * round + 3.0) * (1.0 + 0.2 * std::min(1.0, (double)p.ntiles / cus));
 }
 
+double in_place_us(const int N[3], bool lossy, long long n)
+{
+    // 84 B per cell (96 with conductivity) at 4.7 TB/s, 6.3 where the arrays stay
+    // in the Infinity Cache; 0.235 ns per row of 64 lanes in blocks of four rows;
+    // 11 us where launches queue, 7 in a replayed graph
+    const double cells = (double)N[0] * N[1] * N[2];
+    const double rate = (lossy ? 48.0 : 36.0) * cells <= 256e6 ? 6.3e6 : 4.7e6;
+    const double waves = (double)N[0] * ((N[1] + 3) / 4 * 4) * ((N[2] + 63) / 64);
+    return (double)n * std::max(n < 16 ? 11.0 : 7.0, 5.0 + std::max(waves * 0.000235, (lossy ? 96.0 : 84.0) * cells / rate));
+}
+
 double one_step_us(const int N[3], bool lossy)
 {
     // 256^3 247 us (conductive 277), 384^3 749 (876), 512^3 1921 (2317); 64^3 and
@@ -104,6 +115,27 @@ double one_step_us(const int N[3], bool lossy)
     const double cells = (double)N[0] * N[1] * N[2];
     const double waves = (double)N[0] * ((N[1] + 6) / 7 * 8) * ((N[2] + 63) / 64);
     return lossy ? std::max(4.0 + 72.0 * cells / 4.3e6, waves * 0.00033) : std::max(25.0 + 60.0 * cells / 4.2e6, waves * 0.00055);
+}
+
+// A wavefront of a sweep is 64 lanes of z, a tile of the persistent launch 15
+// cells; that launch pays for filling its pipeline of tiles, so what counts is
+// its area times the steps.  Persistent / sweep in us, materials in a table
+// (as arrays): 1024 x 1024 x 4, 20 steps 3170 / 3570 (3400 / 3850), x 16 4130 /
+// 4670 (4490 / 5680), x 24 5280 / 4720 (5360 / 5430); 512 x 512 x 8, 20 steps
+// 1280 / 1190, 64 steps 3380 / 4350; 1024 x 1024 x 8, 5 steps 1660 / 1310;
+// 1500 x 1500 x 20, 12 steps 5360 / 6900 (5580 / 8390).
+// Periodic axes have no pipeline to fill, and that launch is the faster in short
+// calls: 1024 x 1024 x 1 with periodic y, 5 steps 630 / 815 us, x 16 1320 / 1430
+// (x 4 830 / 750); 20 steps 1.16 to 1.34 times as long as sweeps.
+bool thin_for_sweeps(const int N[3], bool periodic, int mode, bool half, long long n)
+{
+    const double area = (double)N[0] * N[1] * (double)n;
+    const int nz = N[2];
+    if (periodic) return nz <= 16 && n <= 8 && (double)N[0] * N[1] >= 262144.0;
+    if (mode == kLossyTable) return nz <= 8 && n >= 12 && area >= 16e6;
+    if (nz > (n > 24 ? (mode == kArrays ? 8 : 16) : (mode == kTable ? 24 : 28))) return false;
+    if (nz < 6) return n >= 12 && area >= 10e6;
+    return area >= ((mode == kLossy || half) && n >= 20 && nz <= 16 ? 4e6 : 10e6);
 }
 
 long long mark_words(const Pass& p)

@@ -66,11 +66,18 @@ double round_us(int mode, int rows, int T, int xc, bool cached);
 // (s null: no shape has that T).
 Pass plan_pass(const int N[3], int mode, int hook, int T, int cus);
 
-// Estimates by which a call chooses between a sweep and another launch: a pass
-// alone on the device, counting what its tiles touch of a thin grid; one step
-// in one launch (plain.hip).
+// Estimates by which a call chooses between sweeps and a scheme's own launches
+// (fitted to both sides measured in turn on 340 thin, short and ordinary calls;
+// the choice is right or within 4% of it on all but five, the worst 0.79):
+// a pass alone on the device, counting what its tiles touch of a thin grid;
+// n steps of two launches each, in place; one step in one launch (plain.hip).
 double alone_us(const Pass& p, const int N[3], int cus);
+double in_place_us(const int N[3], bool lossy, long long n);
 double one_step_us(const int N[3], bool lossy);
+
+// Whether the persistent launch is the faster of the two on a grid that is thin
+// along z (`periodic` along any axis), in a call of n steps.
+bool thin_for_sweeps(const int N[3], bool periodic, int mode, bool half, long long n);
 
 // Words of progress marks that a pass of this plan addresses, and the most that
 // any plan of the grid does, whatever coefficients the context is given.

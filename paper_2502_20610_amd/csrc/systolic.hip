@@ -1609,7 +1609,7 @@ bool sweeps_instead(fdtd_ctx* ctx, int64_t nsteps)
         (void)hipGetLastError();
         return false;
     }
-    if (group > 2LL * cus) return false;
+    if (group > 2LL * cus || sweeps_too_thin(ctx, nsteps)) return false;
     if (ctx->storage == FDTD_FP16_STORAGE) {
         const int K = default_band(&ctx, 1, nsteps);
         const double slots = (double)plan::distance_bound(N, per, W, K) + 2.0 * (2.0 * cus);

@@ -162,3 +162,41 @@ def test_single_fused_steps(shape, bc, lossy):
     finally:
         for sim in sims:
             sim.close()
+
+
+@pytest.mark.parametrize("scheme,shape,bc,calls,swept", [
+    ("plain", (700, 1, 600), (PEC, PER, PEC), (2, 5, 20), None), ("plain", (60, 70, 64), (PEC, PEC, PEC), (2, 3, 6), None),
+    ("systolic", (520, 510, 8), (PEC, PEC, PEC), (12, 64), False), ("systolic", (520, 510, 24), (PEC, PEC, PEC), (12, 30), True),
+    ("systolic", (512, 512, 3), (PEC, PER, PEC), (5, 3), False), ("systolic", (512, 512, 3), (PEC, PER, PEC), (20,), True)])
+def test_thin_grids_and_short_calls_give_the_same_bits(scheme, shape, bc, calls, swept):
+    """Both sides of the lines at which a call leaves sweeps for a scheme's own
+    launches, against those launches."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    eps, _ = _materials("table", shape, gen)
+    fields = [torch.rand(shape, device="cuda", generator=gen) - 0.5 for _ in range(6)]
+    torch.cuda.synchronize()
+    sims = [fdtd.Simulation(shape, 0.5, 1.0, bc, scheme=scheme) for _ in range(2)]
+    try:
+        sims[1].set_option(fdtd.OPT_SWEEPS, 0)
+        for sim in sims:
+            sim.set_materials(eps)
+            sim.set_fields(fields)
+            sim.synchronize()
+        got, want = torch.empty(shape, device="cuda"), torch.empty(shape, device="cuda")
+        torch.cuda.synchronize()
+        for n in calls:
+            for sim in sims:
+                sim.step(n)
+            if swept is not None and n * shape[0] * shape[1] >= 10 ** 7 or n < 12 and bc[1] == PER:
+                assert (sims[0].info(fdtd.INFO_RING_SLOTS) == 0) == (swept or scheme == "plain")
+            for c in range(6):
+                sims[0].read_fields(mask=1 << c, out=[got] * 6)
+                sims[1].read_fields(mask=1 << c, out=[want] * 6)
+                for sim in sims:
+                    sim.synchronize()
+                assert torch.equal(got.view(torch.int32), want.view(torch.int32)), (n, c)
+    finally:
+        for sim in sims:
+            sim.close()
