@@ -922,14 +922,21 @@ int fdtd_read_fields(fdtd_ctx* ctx, uint32_t comp_mask, float* const dst[6], int
     size_t size[6];
     int m = 0;
     for (int c = 0; c < 6 && here; ++c) {
+        if (!(comp_mask >> c & 1u)) continue;
+        to[m] = (uintptr_t)dst[c];
+        if (m > 0 && to[m] >= base[m - 1] && to[m] - base[m - 1] < size[m - 1]) {
+            // (the allocation of the one before)
+            base[m] = base[m - 1];
+            size[m] = size[m - 1];
+            ++m;
+            continue;
+        }
         hipPointerAttribute_t at;
         hipDeviceptr_t b = nullptr;
-        if (!(comp_mask >> c & 1u)) continue;
         here = hipPointerGetAttributes(&at, dst[c]) == hipSuccess && at.type == hipMemoryTypeDevice &&
                at.device == ctx->device && hipMemGetAddressRange(&b, &size[m], dst[c]) == hipSuccess;
         if (!here) (void)hipGetLastError();
-        base[m] = (uintptr_t)b;
-        to[m++] = (uintptr_t)dst[c];
+        base[m++] = (uintptr_t)b;
     }
     here = here && writable_at_once(to, base, size, m, bytes);
     if (here) {
