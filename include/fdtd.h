@@ -465,7 +465,9 @@ enum {
     FDTD_KERNEL_PLAIN_H = 1,   /* plain H half-step                        */
     FDTD_KERNEL_SOURCES = 2,   /* plain-scheme point-source injection      */
     FDTD_KERNEL_SYSTOLIC = 3,  /* persistent systolic kernel               */
-    FDTD_KERNEL_PLAIN_FUSED = 4, /* fused plain step (one launch per step) */
+    FDTD_KERNEL_PLAIN_FUSED = 4, /* fused plain step (one launch per step with
+                                    per-kernel timing on), and the sweeps of
+                                    fdtd_adjoint's forward run            */
     FDTD_KERNEL_COUNT = 5
 };
 

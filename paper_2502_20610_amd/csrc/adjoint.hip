@@ -295,7 +295,8 @@ void column_grid(const fdtd_ctx* ctx, dim3* grid, int* xchunk)
 // Device buffers of one adjoint call, freed on every exit path.
 struct Work {
     float* ckpt = nullptr;   // checkpoints of segments 0..nseg-2, then the final state
-    float* lam = nullptr;    // 6 adjoint fields (12 with sweeps)
+    float* lam = nullptr;    // 6 adjoint fields
+    float* lam2 = nullptr;   // sweeps: the second set of them
     double* F = nullptr;     // monitor transform, re/im
     float* hist = nullptr;   // S x (3 or 6) x design cells: CH(H^{n-1/2}) (and E^{n-1})
     double* g = nullptr;     // (3 or 6) x design cells: dJ/dcE (and dJ/dA)
@@ -303,7 +304,7 @@ struct Work {
     float* back = nullptr;   // sweeps: adjoint E over the design box, one record per step of a run
     ~Work()
     {
-        for (void* p : {(void*)ckpt, (void*)lam, (void*)F, (void*)hist, (void*)g, (void*)out, (void*)back})
+        for (void* p : {(void*)ckpt, (void*)lam, (void*)lam2, (void*)F, (void*)hist, (void*)g, (void*)out, (void*)back})
             if (p) (void)hipFree(p);
     }
 };
@@ -376,6 +377,24 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
         (void)hipGetLastError();
         return fail(ctx, FDTD_ENOMEM, std::string("adjoint working memory: ") + hipGetErrorString(e));
     }
+    // Sweeps where the grid and the memory allow them (a second set of fields
+    // and of adjoint fields); the one-step kernels otherwise.  Same operations on
+    // every cell: the results are the same.  Few steps do not earn the second
+    // sets' allocation (128^3, 2 steps 0.34 ms in single steps, 0.79 as sweeps, 10
+    // steps 0.99 / 1.24, 20 steps 1.72 / 1.62; 64^3, 4 steps 0.29 / 0.26); boxes
+    // that cover the grid leave no plain blocks, and the sums go cell by cell
+    // (design and monitor both whole, 64^3 2.9 / 3.4 ms, 128^3 18.2 / 22.4; the
+    // design alone 2.4 / 2.3, 7.5 / 6.4); of a grid thin along z a tile uses few
+    // lanes (512 x 512 x 8 7.3 / 9.2 ms).
+    const bool thin = ctx->nz >= 6 && ctx->nz <= 16 && (double)ctx->nx * ctx->ny >= 262144.0;
+    bool swept = N > (nc <= ((size_t)1 << 18) ? 3 : 15) && (double)(ndes + nmon) <= 1.5 * (double)nc && !thin && sweep_hooked_ready(ctx);
+    // reverse steps between two additions to the gradient: records of 64 MB at most
+    const int64_t run = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(N, 64), (int64_t)(64e6 / (12.0 * (double)ndes))));
+    if (swept && (hipMalloc(&w.lam2, 6 * nc * sizeof(float)) != hipSuccess ||
+                  hipMalloc(&w.back, (size_t)run * 3 * (size_t)ndes * sizeof(float)) != hipSuccess)) {
+        (void)hipGetLastError();
+        swept = false;
+    }
     hipStream_t st = ctx->stream;
     auto copy_state = [&](float* dst_base, bool to_ckpt) -> hipError_t {
         for (int c = 0; c < 6; ++c) {
@@ -386,24 +405,6 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
         }
         return hipSuccess;
     };
-    // Sweeps where the grid and the memory allow them (a second set of fields
-    // and of adjoint fields); the one-step kernels otherwise, and for a single
-    // step.  Same operations on every cell: the results are the same.
-    bool swept = N > 1 && sweep_hooked_ready(ctx);
-    // reverse steps between two additions to the gradient: records of 64 MB at most
-    const int64_t run = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(N, 64), (int64_t)(64e6 / (12.0 * (double)ndes))));
-    if (swept) {
-        float* twice = nullptr;
-        if (hipMalloc(&twice, 12 * nc * sizeof(float)) == hipSuccess &&
-            hipMalloc(&w.back, (size_t)run * 3 * (size_t)ndes * sizeof(float)) == hipSuccess) {
-            (void)hipFree(w.lam);
-            w.lam = twice;
-        } else {
-            (void)hipGetLastError();
-            if (twice) (void)hipFree(twice);
-            swept = false;
-        }
-    }
     SweepHooks hooks{};
     for (int a = 0; a < 3; ++a) {
         hooks.mon_lo[a] = mon.lo[a];
@@ -473,7 +474,7 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
     float* lam2[6];
     for (int c = 0; c < 6; ++c) {
         lam[c] = w.lam + c * nc;
-        lam2[c] = swept ? w.lam + (6 + c) * nc : nullptr;
+        lam2[c] = swept ? w.lam2 + c * nc : nullptr;
     }
     if ((e = hipMemsetAsync(w.lam, 0, 6 * nc * sizeof(float), st)) != hipSuccess ||
         (e = hipMemsetAsync(w.g, 0, nrec * (size_t)ndes * sizeof(double), st)) != hipSuccess)

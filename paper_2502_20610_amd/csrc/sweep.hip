@@ -397,7 +397,10 @@ int sweep_forward(fdtd_ctx* ctx, const SweepHooks& h, int64_t n0, int64_t n, boo
             A.out[c] = ctx->alt[c];
         }
         A.step = ctx->step_count;
+        PendingTiming t;
+        timing_begin(ctx, FDTD_KERNEL_PLAIN_FUSED, &t);
         launch_pass(ctx, S->forward[T], A, &K);
+        timing_end(ctx, &t);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(ctx, e, "launch(adjoint forward sweep)");
         for (int c = 0; c < 6; ++c) std::swap(ctx->field[c], ctx->alt[c]);

@@ -160,3 +160,36 @@ def test_half_storage_takes_little_memory_for_sweeps():
             assert (taken > 24 * plane * shape[0]) == swept
         finally:
             sim.close()
+
+
+def test_adjoint_forward_run_is_timed():
+    """Per-kernel timing counts the forward run's launches, swept or single."""
+    w = wl.small_case((40, 36, 44), (PEC, PEC, PEC), seed=5, nsteps=30, dipoles=[(8, 12, 18)])
+    for sweeps in (0, 1):
+        sim = _sim(w, "plain", [(fdtd.OPT_SWEEPS, sweeps), (fdtd.OPT_PROFILE, 1)])
+        try:
+            sim.adjoint(24, 2, (30, 3, 2), (31, 30, 40), 0.4, (12, 5, 6), (19, 17, 30))
+            single, swept = sim.kernel_stats(fdtd.KERNEL_PLAIN_E), sim.kernel_stats(fdtd.KERNEL_PLAIN_FUSED)
+            assert single[0] == (0 if sweeps else 24)
+            assert (6 <= swept[0] <= 24 and swept[1] > 0.0) if sweeps else swept[0] == 0
+        finally:
+            sim.close()
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5])
+@pytest.mark.parametrize("boxes", ["small", "design whole", "both whole"])
+def test_adjoint_at_the_lines_between_the_two_ways(n, boxes):
+    shape = (20, 24, 30)
+    w = wl.small_case(shape, (PEC, PEC, PEC), seed=15, nsteps=n, dipoles=[(8, 12, 18)])
+    mon = ((0, 0, 0), shape) if boxes == "both whole" else ((14, 0, 0), (15, 24, 30))
+    des = ((6, 5, 6), (9, 9, 9)) if boxes == "small" else ((0, 0, 0), shape)
+    outs = []
+    for sweeps in (0, 1):
+        sim = _sim(w, "plain", [(fdtd.OPT_SWEEPS, sweeps)])
+        try:
+            J, g = sim.adjoint(n, 2, *mon, 0.4, *des)
+            outs.append((J, g, sim.read_fields()))
+        finally:
+            sim.close()
+    assert outs[0][0] == outs[1][0] and np.array_equal(outs[0][1].view(np.uint32), outs[1][1].view(np.uint32))
+    assert_bitwise(outs[0][2], outs[1][2], "state after the adjoint")
