@@ -171,7 +171,10 @@ int fdtd_set_materials(fdtd_ctx* ctx, const float* eps_x, const float* eps_y,
  * fdtd_step_batch refuses (FDTD_EUNSUPPORTED) a batch that mixes
  * conductive and lossless contexts; fdtd_adjoint differentiates the
  * conductive update with respect to eps, sigma held fixed.  A later
- * fdtd_set_materials makes the context lossless again. */
+ * fdtd_set_materials makes the context lossless again.  As there, the library
+ * looks for at most 256 distinct entries, here of (cE, ca), for sweeps
+ * (synchronising the stream; 0.1 to 0.7 ms for 2^15 to 45 M cells; without
+ * room, or in a captured stream, the arrays serve). */
 int fdtd_set_lossy_materials(fdtd_ctx* ctx, const float* eps_x, const float* eps_y,
                              const float* eps_z, const float* sigma_x, const float* sigma_y,
                              const float* sigma_z, int where);

@@ -251,9 +251,10 @@ int invariants_scratch_init(int device);
 double* invariants_scratch_ptr(int device);
 
 // Material indices (materials.hip): find the distinct coefficient triples
-// of a lossless context after its coefficients were built (FP32 values; the
-// exact FP32 values of binary16 ones with FP16 storage); leaves nmat = 0
-// when there are more than kMaxMaterials (or the context is conductive).
+// of a context after its coefficients were built (FP32 values; the exact FP32
+// values of binary16 ones with FP16 storage; with conductivity the sixes of
+// (cE, ca)).  Leaves nmat = 0 when there are more than kMaxMaterials or the
+// context is conductive, ntab8 = 0 when the one-byte form is not to be had.
 // release_material_ids frees them.
 constexpr int kMaxMaterials = 256;
 int build_material_ids(fdtd_ctx* ctx);

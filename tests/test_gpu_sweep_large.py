@@ -200,3 +200,33 @@ def test_thin_grids_and_short_calls_give_the_same_bits(scheme, shape, bc, calls,
     finally:
         for sim in sims:
             sim.close()
+
+
+@pytest.mark.parametrize("lossy", [False, True])
+@pytest.mark.parametrize("count", [17, 255, 256, 700])
+def test_tables_of_many_materials(count, lossy):
+    """More distinct cells in a wavefront than it reports in a round, up to the
+    largest table, one more, and many more (the arrays serve), against the
+    oracle."""
+    import numpy as np
+
+    import oracle
+    from tests.test_gpu_parity import assert_bitwise
+    shape, bc = (30, 22, 61), (PER, PER, PER)
+    rng = np.random.default_rng(count)
+    which = rng.integers(0, count, shape)
+    which.reshape(-1)[:count] = np.arange(count)
+    eps = (1.0 + which / np.float32(32)).astype(np.float32)
+    sigma = (which / np.float32(4096)).astype(np.float32) if lossy else None
+    fields = [rng.uniform(-1, 1, shape).astype(np.float32) for _ in range(6)]
+    sim = fdtd.Simulation(shape, 0.5, 1.0, bc, scheme="plain")
+    try:
+        for _ in range(2):
+            sim.set_materials(eps, sigma=sigma)
+            assert sim.info(fdtd.INFO_MATERIALS) == (count + 1 if count < 256 and not lossy else 0)
+        sim.set_fields(fields)
+        sim.step(7)
+        ref = oracle.run(fields, [eps] * 3, bc, 0.5, 1.0, 7, dtype=np.float32, sigma=[sigma] * 3 if lossy else None)
+        assert_bitwise(sim.read_fields(), ref, "%d materials, lossy %s" % (count, lossy))
+    finally:
+        sim.close()
