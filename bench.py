@@ -10,7 +10,9 @@ are resident in HBM before the timed region; the timed region is K steps
 bracketed by stream synchronisation.  Prints ONE JSON line for the headline
 scheme (systolic when available, else plain), with the two plain schemes'
 figures alongside (timed kernel by kernel, which keeps them at one launch per
-half-step and one per step; untimed calls sweep several), a roofline object for the dominant kernel (per-launch
+half-step and one per step; `as_called_cups` is the same call untimed, which
+sweeps several steps, and `persistent_cups` the systolic scheme with sweeps
+off), a roofline object for the dominant kernel (per-launch
 device time from HIP events recorded on the library's stream inside the
 timed region) and the oracle timed on the host cores over a bounded sample.
 """
@@ -202,9 +204,28 @@ def run_scheme(w, scheme: str, steps: int, warmup: int, options=None, sigma=None
                              "tile": [sim.info(fdtd.INFO_TILE_X), sim.info(fdtd.INFO_TILE_Y),
                                       sim.info(fdtd.INFO_TILE_Z)]}
         log("%s: %d steps in %.3f s" % (scheme, steps, t))
+        if profile:
+            # beside it, untimed per kernel: a plain scheme's call as a program
+            # makes it, and the persistent launch where the timed call swept
+            swept = scheme == "systolic" and stats["info"]["ring_slots"] == 0
+            if scheme != "systolic" or swept:
+                sim.set_option(fdtd.OPT_PROFILE, 0)
+                if swept:
+                    sim.set_option(fdtd.OPT_SWEEPS, 0)
+                stats["beside_s"] = _time_call(sim, steps)
         return t, stats
     finally:
         sim.close()
+
+
+def _time_call(sim, steps: int) -> float:
+    sim.prepare(steps)
+    sim.step(steps)
+    sim.synchronize()
+    t0 = time.perf_counter()
+    sim.step(steps)
+    sim.synchronize()
+    return time.perf_counter() - t0
 
 
 def cpu_baseline(w, budget_s: float = 25.0):
@@ -660,9 +681,15 @@ def main():
             pb = PLAIN_FUSED_BYTES_PER_UPDATE + (12 if sigma is not None else 0)
             entry["alg_bytes_per_update"] = pb
             entry["alg_roofline_frac"] = c * pb / (HBM_PEAK_GBS * 1e9)
+        if "beside_s" in st:
+            name = "persistent_cups" if scheme.startswith("systolic") else "as_called_cups"
+            entry[name] = cells * args.steps / st["beside_s"]
         out[scheme] = entry
+    # (over the plain schemes kernel by kernel; over their calls below)
     if "plain" in results and "systolic" in results:
         out["systolic_over_plain"] = out["systolic"]["cups"] / out["plain"]["cups"]
+        if "as_called_cups" in out["plain"]:
+            out["systolic_over_plain_as_called"] = out["systolic"]["cups"] / out["plain"]["as_called_cups"]
     if "plain_fused" in results and "systolic" in results:
         out["systolic_over_plain_fused"] = out["systolic"]["cups"] / out["plain_fused"]["cups"]
     if "plain_fused" in results and "systolic_arrays" in results:
