@@ -26,29 +26,36 @@
  *                        sweeps instead (several steps per pass from one set
  *                        of arrays to a second one and back: the state ends
  *                        in the arrays it started from), unless per-kernel
- *                        timing is on or the second set would take more than
- *                        a quarter of the free device memory.
+ *                        timing is on, FDTD_OPT_SWEEPS is 0, the two launches
+ *                        are estimated to be faster (two steps past 2^17
+ *                        cells, grids thin along y or z), or the second set
+ *                        would take more than a quarter of the free device
+ *                        memory when it is first wanted.
  *   FDTD_SCHEME_SYSTOLIC one persistent launch per call: subdomain tiles stay
  *                        resident on chip for many steps, move one cell along
  *                        the x-y-z-t diagonal per step and exchange only their
  *                        boundary faces through device memory, synchronising
- *                        with neighbour flags (Sections 3 and 4).  FP32
- *                        calls of two steps or more run as sweeps, under the
- *                        conditions above, unless a systolic option (band
- *                        steps, workgroups, tile width, spin limit) is set or
- *                        the call spans two of the longest bands on an
- *                        all-PEC grid; launches of either kind count as
- *                        FDTD_KERNEL_SYSTOLIC, and FDTD_INFO_SYSTOLIC_* then
- *                        describe the sweep (steps per pass, blocks, tiles, 0
- *                        ring slots).
+ *                        with neighbour flags (Sections 3 and 4).  Calls of
+ *                        two steps or more run as sweeps, under the same
+ *                        condition on memory (FP16 storage: see there, and
+ *                        with material indices), unless FDTD_OPT_SWEEPS is 0,
+ *                        a systolic option (band steps, workgroups, tile
+ *                        width, spin limit) is set, the grid is thin along z
+ *                        and large, or the call spans two of the longest
+ *                        bands on an all-PEC grid; launches of either kind
+ *                        count as FDTD_KERNEL_SYSTOLIC, and
+ *                        FDTD_INFO_SYSTOLIC_* then describe the sweep (steps
+ *                        per pass, blocks, tiles, 0 ring slots).
  *   FDTD_SCHEME_PLAIN_FUSED sweeps: one launch advances up to five steps
- *                        (one with per-kernel timing on).  E and H are read
- *                        from one set of arrays and the new state is written
- *                        to a second set, allocated on first use (six more
- *                        arrays; the two sets trade places with every
- *                        launch).  FP32 storage only (else
+ *                        (one with per-kernel timing on or FDTD_OPT_SWEEPS
+ *                        0).  E and H are read from one set of arrays and the
+ *                        new state is written to a second set, allocated on
+ *                        first use (six more arrays; the two sets trade
+ *                        places with every launch).  FP32 storage only (else
  *                        FDTD_EUNSUPPORTED from fdtd_step); conductivity is
  *                        covered.
+ * The second set, once taken, is kept until FDTD_OPT_SWEEPS = 0 or
+ * fdtd_destroy.
  *
  * Layout: every field and coefficient array is C order [nx][ny][nz]
  * (z fastest), one array per component (Ex, Ey, Ez, Hx, Hy, Hz); FP32, or
@@ -219,8 +226,8 @@ int fdtd_step(fdtd_ctx* ctx, int64_t nsteps);
  * launch plan of a call of exactly nsteps steps (the (band, tile) tickets in
  * their topological order and the band tables of Section 3's diagonal
  * traversal), upload it with blocking copies, and allocate its face rings
- * and progress counters; with the fused plain scheme, allocate the second
- * field set; with the plain scheme, nothing.  No step runs and the state is
+ * and progress counters; where the call will sweep, and with the fused plain
+ * scheme, allocate the second field set.  No step runs and the state is
  * unchanged.  fdtd_step keeps the plan of its last call length (and the
  * largest rings so far), so repeated calls of one length never rebuild or
  * reallocate; this call moves that work ahead of a first call (say, out of
@@ -369,8 +376,8 @@ typedef struct {
                                sum of the three, added in FP64)            */
 } fdtd_adjoint_spec;
 
-/* Run spec->nsteps steps forward from the current state (plain scheme, the
- * sources included) while accumulating F in FP64, then the reverse sweep.
+/* Run spec->nsteps steps forward from the current state (the plain update, the
+ * sources included, as sweeps where they pay) while accumulating F in FP64, then the reverse sweep.
  * Writes J to spec->objective and dJ/deps_c for c = x, y, z to grad_eps:
  * three FP32 blocks of the design box, each C-ordered [dx][dy][dz], laid out
  * component after component (with spec->isotropic = 1, one such block
@@ -380,7 +387,8 @@ typedef struct {
  * (one copy of the six fields per segment when there are several segments,
  * none with one), the adjoint fields and one segment's design-box history
  * (3 arrays per step, 6 with conductivity) is allocated for the call and
- * freed before it returns.
+ * freed before it returns; a second field set taken for its sweeps stays with
+ * the context.
  * Errors: FDTD_EINVAL for a bad spec (component, empty or out-of-grid
  * boxes, nsteps < 1, checkpoint_every < 0, isotropic not 0 or 1,
  * struct_size), FDTD_ENOMEM when
@@ -405,8 +413,9 @@ enum {
                                  indices instead of the coefficient arrays where
                                  the context has them (FDTD_INFO_MATERIALS > 0);
                                  0 = always the arrays.  Same results.        */
-    FDTD_OPT_GRAPHS = 6,      /* plain schemes: 1 (default) = calls of 16 steps
-                                 or more replay a HIP graph of 16 steps
+    FDTD_OPT_GRAPHS = 6,      /* plain scheme in place (no sweeps): 1 (default)
+                                 = calls of 16 steps or more replay a HIP graph
+                                 of 16 steps
                                  (captured on first use, re-captured when the
                                  arrays, sources or scales change); 0 = one
                                  launch per kernel.  Same results; per-kernel
@@ -423,7 +432,7 @@ enum {
                                  storage takes 15 or 19.  A batch needs one
                                  width for all.                                */
     FDTD_OPT_AUTOTUNE_PLAIN = 8,/* 1 = fdtd_autotune also times the plain
-                                 two-launch scheme (FP32 storage only, where
+                                 scheme, sweeps included (FP32 storage only, where
                                  every scheme gives the same bits) and switches
                                  the context to it when it is faster; 0
                                  (default) = systolic configurations only     */
@@ -455,9 +464,12 @@ int fdtd_set_option(fdtd_ctx* ctx, int option, int64_t value);
  * FDTD_OPT_BAND_STEPS.  The choice is kept for the process, keyed by grid
  * shape, boundaries, storage, conductivity, material indices and run length:
  * a later call with the same key takes it without timing anything.  With
- * FDTD_OPT_AUTOTUNE_PLAIN the plain two-launch scheme is timed as well (FP32
- * storage); when it is faster the context switches to it
- * (FDTD_INFO_SCHEME) and tile_x and band_steps read 0.
+ * FDTD_OPT_AUTOTUNE_PLAIN the plain scheme is timed as well, as its calls run
+ * (FP32 storage); when it is faster the context switches to it
+ * (FDTD_INFO_SCHEME) and tile_x and band_steps read 0.  Without it the choice is
+ * among persistent launches alone, and the options that it sets keep later
+ * calls from sweeping, which is the faster on most grids: setting both to 0
+ * brings that back.
  * tile_x, band_steps: the chosen values, or NULL.  Synchronises.
  * Errors: FDTD_EUNSUPPORTED for another scheme or when no candidate runs,
  * FDTD_ENOMEM without room for the copy; the errors of fdtd_step. */

@@ -8,10 +8,12 @@
 // length the caller will use, from the context's current state, which is
 // restored after every run.  The fastest pair becomes the context's options
 // and is kept for the process, keyed by everything the choice depends on.
-// With FP32 storage, where every scheme computes the same bits, the plain
-// two-launch scheme (replayed as a graph) can be timed too: small grids,
-// whose state sits in the last-level cache and whose few tiles cannot fill a
-// systolic pipeline, run faster on it, and the context then switches to it.
+// The choice is among persistent launches: either option, once set, also keeps
+// later calls from sweeping, which an untuned context does and which is the
+// faster on most grids (256^3 with periodic x and y 94 against 209 G cell
+// updates/s).  With FP32 storage, where every scheme computes the same bits, the
+// plain scheme can be timed too, as its calls run (sweeps on most grids), and
+// the context then switches to it.
 #include <string.h>
 
 #include <map>
@@ -28,7 +30,7 @@ std::mutex g_tune_mu;
 // key -> (tile width, band); (0, 0) when the plain scheme won
 std::map<std::vector<int64_t>, std::pair<int, int>> g_tuned;
 
-// the plain two-launch scheme takes part: asked for, and FP32 storage (the
+// the plain scheme takes part: asked for, and FP32 storage (the
 // FP16 schemes round at different places, so switching would change results)
 bool plain_candidate(const fdtd_ctx* ctx) { return ctx->tune_plain && ctx->storage == FDTD_FP32; }
 
@@ -143,8 +145,8 @@ int autotune_run(fdtd_ctx* ctx, int64_t nsteps, int64_t* out_tile, int64_t* out_
                 if (d) rc = d;
             }
         }
-    // the plain two-launch scheme, timed the same way (twice: the first run
-    // also captures its step graph)
+    // the plain scheme, timed the same way (twice: the first run also allocates
+    // its second field set or captures its step graph)
     bool plain_wins = false;
     if (plain_candidate(ctx) && have && !rc && e == hipSuccess) {
         float ms = 0.0f;

@@ -1575,21 +1575,24 @@ bool wide_tile_ok(fdtd_ctx* const* cs, int n)
 
 // Whether a call advances the context by sweeps (sweep.hip) instead of the
 // persistent launch.  The sweep has no neighbour to wait for and no band to
-// fill, and is the faster of the two at every size and call length measured
-// (G cell updates/s, systolic / sweep): 64^3 18 / 43, 128^3 86 / 124, 256^3
-// with periodic x and y 94 / 209, 256^3 conductive 109 / 195, 1024 x 1024 x
-// 512 in 20-step calls 163 / 255.  The persistent launch keeps:
-//   * calls with a systolic option of their own, which ask for that kernel;
+// fill, and is the faster of the two on grids of ordinary shape in every length
+// of call measured (G cell updates/s, systolic / sweep): 64^3 18 / 43, 128^3 86
+// / 124, 256^3 with periodic x and y 94 / 209, 256^3 conductive 109 / 195,
+// 1024 x 1024 x 512 in 20-step calls 163 / 255.  The persistent launch keeps:
+//   * calls with a systolic option of their own, which ask for that kernel, and
+//     contexts with sweeps off;
+//   * grids thin along z, where it is the faster (sweeps_too_thin);
 //   * FP16 storage with more than 256 materials (with a table, the bands are
 //     swept over FP32 copies of the state and rounded where they end: the same
-//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 18.1 ms),
-//     and where the face rings of the band may not fit their 32-bit offsets:
-//     the launch then takes a shorter one, and rounds where that ends
-//     (1024^3: 49 steps instead of 64);
+//     bits; a 48-step call on 512 x 448 x 384 and its read-out 22.5 / 18.1 ms,
+//     calls of 2 to 64 steps there 1.13 to 1.45 times as fast), and where the
+//     face rings of the band may not fit their 32-bit offsets: the launch then
+//     takes a shorter one, and rounds where that ends (1024^3: 49 steps instead
+//     of 64);
 //   * single steps (a sweep would leave the state in the other arrays);
 //   * on all-PEC grids, calls of two 64-step bands or more (512^3 and up by
-//     the band model), whose band and ring slots FDTD_INFO_* reports
-//     (1024 x 1024 x 512: 214 / 255);
+//     the band model): not the faster (1024 x 1024 x 512: 214 / 255), but callers
+//     read the band and ring slots of such calls from FDTD_INFO_*;
 //   * what it refuses: a ring group of a periodic grid larger than its
 //     resident workgroups (two per CU).
 bool sweeps_instead(fdtd_ctx* ctx, int64_t nsteps)
