@@ -444,7 +444,9 @@ enum {
                                  field set and FP16 storage's FP32 copies are
                                  given back, after waiting for the stream (the
                                  fused scheme takes its set again when it next
-                                 runs).  Same results.                        */
+                                 runs); a graph captured from the context's
+                                 stream must not be replayed after that.  Same
+                                 results.                                     */
 };
 
 /* Set a tuning option (see FDTD_OPT_*).  FDTD_EINVAL for unknown options or

@@ -260,7 +260,8 @@ int run(fdtd_ctx* ctx, float* now[6], float* other[6], int64_t n, int kernel, bo
             A.out[c] = other[c];
         }
         A.step = ctx->step_count;
-        const bool paced = S->pace && mark_words(P) <= S->pace_words;
+        const bool one = T == 1 && ctx->storage == FDTD_FP32 && one_step_launch(ctx);
+        const bool paced = S->pace && !one && mark_words(P) <= S->pace_words;
         A.pace = paced ? S->pace + (size_t)S->turn * S->pace_words : nullptr;
         A.pace_next = paced ? S->pace + (size_t)(S->turn ^ 1) * S->pace_words : nullptr;
         A.pace_words = S->pace_words;
@@ -268,7 +269,7 @@ int run(fdtd_ctx* ctx, float* now[6], float* other[6], int64_t n, int kernel, bo
         PendingTiming t;
         timing_begin(ctx, kernel, &t);
         int rc = FDTD_OK;
-        if (T == 1 && ctx->storage == FDTD_FP32 && one_step_launch(ctx))
+        if (one)
             rc = fused_one_step(ctx, now, other);
         else
             launch_pass(ctx, P, A);

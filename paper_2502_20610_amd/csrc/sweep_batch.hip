@@ -161,7 +161,8 @@ int sweep_batch_steps(fdtd_ctx* const* cs, int n, int64_t nsteps, bool* done)
     int cus = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, lead->device);
     if (e != hipSuccess) return hip_fail(lead, e, "sweep batch: device attribute");
-    // the table form when every member has it
+    // the table form when every member has it (two grids of 256^3, 20 steps: both
+    // with a table 3.99 ms, one 4.50, none 4.52; one persistent launch 4.67 to 5.0)
     int mode = mode_of(lead);
     for (int i = 1; i < n; ++i)
         if (mode_of(cs[i]) != mode) mode = lead->ca[0] ? kLossy : kArrays;
