@@ -381,13 +381,15 @@ int adjoint_run(fdtd_ctx* ctx, fdtd_adjoint_spec* spec, float* grad_eps, int whe
     // and of adjoint fields); the one-step kernels otherwise.  Same operations on
     // every cell: the results are the same.  Few steps do not earn the second
     // sets' allocation (128^3, 2 steps 0.34 ms in single steps, 0.79 as sweeps, 10
-    // steps 0.99 / 1.24, 20 steps 1.72 / 1.62; 64^3, 4 steps 0.29 / 0.26); boxes
+    // steps 0.99 / 1.24, 20 steps 1.72 / 1.62; 64^3, 2 steps 0.23 / 0.26, 4 steps
+    // 0.29 / 0.26; 32 x 24 x 28, 2 steps 0.19 / 0.15); boxes
     // that cover the grid leave no plain blocks, and the sums go cell by cell
     // (design and monitor both whole, 64^3 2.9 / 3.4 ms, 128^3 18.2 / 22.4; the
     // design alone 2.4 / 2.3, 7.5 / 6.4); of a grid thin along z a tile uses few
     // lanes (512 x 512 x 8 7.3 / 9.2 ms).
     const bool thin = ctx->nz >= 6 && ctx->nz <= 16 && (double)ctx->nx * ctx->ny >= 262144.0;
-    bool swept = N > (nc <= ((size_t)1 << 18) ? 3 : 15) && (double)(ndes + nmon) <= 1.5 * (double)nc && !thin && sweep_hooked_ready(ctx);
+    const int64_t single = nc <= ((size_t)1 << 16) ? 1 : nc <= ((size_t)1 << 18) ? 3 : 15;
+    bool swept = N > single && (double)(ndes + nmon) <= 1.5 * (double)nc && !thin && sweep_hooked_ready(ctx);
     // reverse steps between two additions to the gradient: records of 64 MB at most
     const int64_t run = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(N, 64), (int64_t)(64e6 / (12.0 * (double)ndes))));
     if (swept && (hipMalloc(&w.lam2, 6 * nc * sizeof(float)) != hipSuccess ||

@@ -176,10 +176,10 @@ def test_adjoint_forward_run_is_timed():
             sim.close()
 
 
-@pytest.mark.parametrize("n", [2, 3, 4, 5])
+@pytest.mark.parametrize("shape,n", [((20, 24, 30), 1), ((20, 24, 30), 2), ((45, 40, 41), 3), ((45, 40, 41), 4),
+                                     ((70, 61, 67), 15), ((70, 61, 67), 16)])
 @pytest.mark.parametrize("boxes", ["small", "design whole", "both whole"])
-def test_adjoint_at_the_lines_between_the_two_ways(n, boxes):
-    shape = (20, 24, 30)
+def test_adjoint_at_the_lines_between_the_two_ways(shape, n, boxes):
     w = wl.small_case(shape, (PEC, PEC, PEC), seed=15, nsteps=n, dipoles=[(8, 12, 18)])
     mon = ((0, 0, 0), shape) if boxes == "both whole" else ((14, 0, 0), (15, 24, 30))
     des = ((6, 5, 6), (9, 9, 9)) if boxes == "small" else ((0, 0, 0), shape)
